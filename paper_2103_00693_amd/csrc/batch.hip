@@ -100,12 +100,28 @@ struct EnumTask {
     uint32_t tiles_per_block;
 };
 
-struct EnumTasks {
-    EnumTask t[kMaxEnumTasks];
-    int32_t num;
+// Tasks of batch_enum_kernel, read by every wave from the kernel arguments
+// before its first store.
+struct alignas(128) VecTask {
+    const uint64_t *basis;
+    const uint64_t *shift;
+    int32_t inst;
+    int32_t n;
+    VecRange g;
+    uint32_t block0;
 };
 
-// Optional stage-1 work carried by a materialise launch: the first `blocks`
+struct alignas(128) EnumTasks {
+    uint32_t first[kMaxEnumTasks];  // first block of tasks 1 .. (~0 past the last)
+    uint32_t blocks;                // blocks of all tasks
+    uint32_t tiles_per_block;
+    uint32_t job_blocks;            // blocks before theirs that run the FactorJob
+    int32_t *status;
+    const int32_t *rank;
+    VecTask t[kMaxEnumTasks];
+};
+
+// Optional stage-1 work carried by a materialise launch: the first job_blocks
 // workgroups factor instances order[first .. first + num) of another batch,
 // one instance per wavefront (W = 1).  The records it writes are not read by
 // the same launch, so there is no dependency inside the launch.
@@ -114,21 +130,21 @@ struct FactorJob {
     const uint8_t *A;
     int32_t first;
     int32_t num;
-    uint32_t blocks;
 };
 
-constexpr int kWavesPerTileBlock = kTileThreads / 64;
+constexpr int kWavesPerVecBlock = kVecThreads / 64;
 
 template <typename T, bool kFactor>
-__global__ __launch_bounds__(kTileThreads, 8) void batch_enum_kernel(EnumTasks tasks, FactorJob job) {
-    constexpr int S = tile_shift<T>();
-    __shared__ uint64_t Bx[64];
-    unsigned int bid = blockIdx.x;
+__global__ __launch_bounds__(kVecThreads, 8) void batch_enum_kernel(EnumTasks tasks, FactorJob job) {
+    uint32_t own_first = tasks.first[threadIdx.x & (kMaxEnumTasks - 1)];
+    uint32_t blocks = tasks.blocks, tpb = tasks.tiles_per_block, job_blocks = tasks.job_blocks;
+    asm("" : "+v"(own_first), "+s"(blocks), "+s"(tpb), "+s"(job_blocks));  // in one wait
+    uint32_t bid = blockIdx.x;
     if constexpr (kFactor) {
-        __shared__ WaveSmem<1> sm[kWavesPerTileBlock];
-        if (bid < job.blocks) {
+        __shared__ WaveSmem<1> sm[kWavesPerVecBlock];
+        if (bid < job_blocks) {
             const int w = threadIdx.x >> 6;
-            const int idx = (int)bid * kWavesPerTileBlock + w;
+            const int idx = (int)bid * kWavesPerVecBlock + w;
             if (idx < job.num) {
                 const int i = job.d.order[job.first + idx];
                 const int n = job.d.n[i];
@@ -137,23 +153,20 @@ __global__ __launch_bounds__(kTileThreads, 8) void batch_enum_kernel(EnumTasks t
             }
             return;
         }
-        bid -= job.blocks;
+        bid -= job_blocks;
     }
-    bid = xcd_block(bid, gridDim.x - (kFactor ? job.blocks : 0u));
-    int k = 0;
-    for (int j = 1; j < tasks.num; ++j)
-        if (tasks.t[j].block0 <= bid) k = j;
-    const EnumTask &t = tasks.t[k];
-    int r;
-    if (!gate(t.status, t.rank, t.begin, t.count, r)) return;
-    load_basis_padded<1>(t.basis, r, Bx, threadIdx.x, blockDim.x);
-    __syncthreads();
-    const uint64_t end = t.begin + t.count;
-    const uint64_t ntiles = ((end - 1) >> S) - (t.begin >> S) + 1;
-    const uint64_t t0 = (uint64_t)(bid - t.block0) * t.tiles_per_block;
-    if (t0 >= ntiles) return;
-    const uint64_t t1 = (t0 + t.tiles_per_block < ntiles) ? t0 + t.tiles_per_block : ntiles;
-    enum_tiles_w1<T>(Bx, t.shift[0], t.begin, t.count, (T *)t.out, t0, t1);
+    bid = xcd_block(bid, blocks);
+    // The task of this block: the first blocks of the others, one per lane,
+    // counted where they are at or before it.  (Fifteen scalar compares cost
+    // 30 scalar issues a wave, and the launch a third of its rate.)
+    const uint64_t le = __ballot(own_first <= bid);
+    const uint32_t k = (uint32_t)__builtin_popcount((uint32_t)le & ((1u << kMaxEnumTasks) - 1u));
+    VecTask t = tasks.t[k];
+    asm("" : "+s"(t.inst), "+s"(t.n), "+s"(t.g.begin), "+s"(t.g.end), "+s"(t.g.ntiles), "+s"(t.g.full0),
+        "+s"(t.g.full1), "+s"(t.block0));
+    const uint32_t t0 = (bid - t.block0) * tpb;
+    const uint32_t t1 = t0 + tpb < t.g.ntiles ? t0 + tpb : t.g.ntiles;
+    vec_materialise<T, false>(tasks.status + t.inst, tasks.rank + t.inst, t.basis, t.shift, t.n, t.g, t0, t1);
 }
 
 // ---------------------------------------------------------------------------
@@ -759,14 +772,13 @@ hlf_status hlf_batch_factor_dense(hlf_batch b, const uint8_t *A_dev, hipStream_t
 namespace {
 
 template <typename T>
-void launch_enum_group(unsigned blocks, const hlf::EnumTasks &tasks, const hlf::FactorJob *job,
-                       hipStream_t stream) {
+void launch_enum_group(const hlf::EnumTasks &tasks, const hlf::FactorJob *job, hipStream_t stream) {
     if (job) {
-        hipLaunchKernelGGL((hlf::batch_enum_kernel<T, true>), dim3(blocks + job->blocks),
-                           dim3(hlf::kTileThreads), 0, stream, tasks, *job);
+        hipLaunchKernelGGL((hlf::batch_enum_kernel<T, true>), dim3(tasks.job_blocks + tasks.blocks),
+                           dim3(hlf::kVecThreads), 0, stream, tasks, *job);
     } else {
-        hipLaunchKernelGGL((hlf::batch_enum_kernel<T, false>), dim3(blocks),
-                           dim3(hlf::kTileThreads), 0, stream, tasks, hlf::FactorJob{});
+        hipLaunchKernelGGL((hlf::batch_enum_kernel<T, false>), dim3(tasks.blocks),
+                           dim3(hlf::kVecThreads), 0, stream, tasks, hlf::FactorJob{});
     }
 }
 
@@ -780,60 +792,48 @@ hlf_status batch_enumerate_impl(hlf_batch b, int32_t num, const int32_t *inst,
         if (b->n[inst[k]] > word_bits) return HLF_EINVAL;
         if (count[k] > 0 && !out[k]) return HLF_EINVAL;
     }
-    const int V = 16 / (word_bits / 8);
-    const int S = word_bits == 16 ? hlf::tile_shift<uint16_t>()
-                  : word_bits == 32 ? hlf::tile_shift<uint32_t>() : hlf::tile_shift<uint64_t>();
-    // Fast tasks go into multi-instance launches; the rest take the general path.
-    std::vector<int> fast;
-    for (int k = 0; k < num; ++k) {
-        if (count[k] == 0) continue;
-        const bool ok = begin[k] % V == 0 && ((uintptr_t)out[k] & 15u) == 0 &&
-                        begin[k] + count[k] >= begin[k];
-        if (ok) {
-            fast.push_back(k);
-        } else {
-            hlf_status s = hlf::launch_enumerate(instance_view(b, inst[k]), begin[k], count[k],
-                                                 word_bits, out[k], stream);
-            if (s != HLF_OK) return s;
-        }
-    }
+    auto range_of = [&](int k) {
+        return word_bits == 16   ? hlf::vec_range<uint16_t>(begin[k], count[k], out[k])
+               : word_bits == 32 ? hlf::vec_range<uint32_t>(begin[k], count[k], out[k])
+                                 : hlf::vec_range<uint64_t>(begin[k], count[k], out[k]);
+    };
+    std::vector<int> todo;
+    for (int k = 0; k < num; ++k)
+        if (count[k] > 0) todo.push_back(k);
     bool job_done = job == nullptr;
-    for (size_t g = 0; g < fast.size() || !job_done; g += hlf::kMaxEnumTasks) {
-        const size_t m = g < fast.size() ? std::min<size_t>(hlf::kMaxEnumTasks, fast.size() - g) : 0;
-        std::vector<uint64_t> tiles(m);
+    for (size_t g = 0; g < todo.size() || !job_done; g += hlf::kMaxEnumTasks) {
+        const size_t m = g < todo.size() ? std::min<size_t>(hlf::kMaxEnumTasks, todo.size() - g) : 0;
         uint64_t total = 0;
-        for (size_t j = 0; j < m; ++j) {
-            const int k = fast[g + j];
-            const uint64_t end = begin[k] + count[k];
-            tiles[j] = ((end - 1) >> S) - (begin[k] >> S) + 1;
-            total += tiles[j];
-        }
-        const uint64_t tpb = hlf::materialise_tiles_per_block(total, hlf::kTileBytes);
+        for (size_t j = 0; j < m; ++j) total += range_of(todo[g + j]).ntiles;
         hlf::EnumTasks tasks;
         std::memset(&tasks, 0, sizeof(tasks));
-        tasks.num = (int)m;
+        const uint32_t tpb = hlf::vec_tiles_per_block(total);
+        tasks.tiles_per_block = tpb;
         uint64_t block = 0;
+        std::fill(tasks.first, tasks.first + hlf::kMaxEnumTasks, ~0u);
         for (size_t j = 0; j < m; ++j) {
-            const int k = fast[g + j];
+            const int k = todo[g + j];
             const int i = inst[k];
-            hlf::EnumTask &t = tasks.t[j];
-            t.status = b->status + i;
-            t.rank = b->rank + i;
+            hlf::VecTask &t = tasks.t[j];
+            t.inst = i;
+            t.n = b->n[i];
             t.basis = b->basis + b->mat_off[i];
             t.shift = b->shift + b->vec_off[i];
-            t.out = out[k];
-            t.begin = begin[k];
-            t.count = count[k];
+            t.g = range_of(k);
             t.block0 = (uint32_t)block;
-            t.tiles_per_block = (uint32_t)tpb;
-            block += (tiles[j] + tpb - 1) / tpb;
+            if (j > 0) tasks.first[j - 1] = (uint32_t)block;
+            // a range without tiles (vec_range) still takes a workgroup for the gate
+            block += t.g.ntiles ? (t.g.ntiles + (uint64_t)tpb - 1) / tpb : 1u;
         }
-        if (block > 0xFFFF0000ull) return HLF_EINVAL;
+        tasks.blocks = (uint32_t)block;
+        tasks.status = b->status;
+        tasks.rank = b->rank;
         const hlf::FactorJob *jb = job_done ? nullptr : job;
         job_done = true;
-        if (word_bits == 16) launch_enum_group<uint16_t>((unsigned)block, tasks, jb, stream);
-        else if (word_bits == 32) launch_enum_group<uint32_t>((unsigned)block, tasks, jb, stream);
-        else launch_enum_group<uint64_t>((unsigned)block, tasks, jb, stream);
+        if (jb) tasks.job_blocks = (uint32_t)((jb->num + hlf::kWavesPerVecBlock - 1) / hlf::kWavesPerVecBlock);
+        if (word_bits == 16) launch_enum_group<uint16_t>(tasks, jb, stream);
+        else if (word_bits == 32) launch_enum_group<uint32_t>(tasks, jb, stream);
+        else launch_enum_group<uint64_t>(tasks, jb, stream);
         if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
     }
     return HLF_OK;
@@ -859,7 +859,6 @@ hlf_status hlf_batch_enumerate_overlap(hlf_batch b, int32_t num, const int32_t *
     job.A = A_next_dev;
     job.first = 0;
     job.num = next->count;
-    job.blocks = (uint32_t)((next->count + hlf::kWavesPerTileBlock - 1) / hlf::kWavesPerTileBlock);
     return batch_enumerate_impl(b, num, inst, begin, count, out, word_bits, &job, stream);
 }
 

@@ -1,17 +1,18 @@
 // Single-instance stage-2 kernels (materialise and reduce) for gfx950; the
 // tile algebra they share with the batched kernels is in stage2.h.
 //
-//   enum_tile_kernel<T>     W = 1, 16/32/64-bit words, begin a multiple of
-//                           the 16-byte vector: per-lane constants in VGPRs,
-//                           one 16-byte nontemporal store per lane per tile,
-//                           blocks walk contiguous tile ranges.
-//   enum_general_kernel     any W, any begin/alignment: z_i from LDS lookup
-//                           tables over the bytes (W = 1) or nibbles (W > 1)
-//                           of i (method of four Russians).
+//   enum_tile_kernel<T>     W = 1, 16/32/64-bit words, any begin and address:
+//                           one 16-byte store per thread (stage2.h).
+//   enum_wide_tile_kernel   W > 1: the tile algebra with one lane per word.
+//   enum_general_kernel     W > 1 at an address that is not a multiple of 8:
+//                           z_i from LDS lookup tables over the nibbles of i
+//                           (method of four Russians).
+//   circuit_tile_kernel<T>  the paper's circuit, W = 1; circuit_wide_kernel W > 1.
 //   reduce_wave_kernel<WW>  W <= 3: every wavefront reduces a contiguous tile
 //                           range (stage2.h); the block combines its waves in
 //                           LDS and adds to the outputs with one atomic each.
 //   reduce_general_kernel   W > 3: element by element.
+#include <algorithm>
 #include <type_traits>
 
 #include "hlf_device.h"
@@ -25,45 +26,12 @@ __device__ __forceinline__ bool gate(const FactorIn &f, uint64_t begin, uint64_t
     return hlf::gate(f.status, f.rank, begin, count, r);
 }
 
-// Counter order (one word per basis vector): Bx[j] <- B_0 ^ ... ^ B_j for
-// j < r, by an inclusive prefix-XOR scan across the 64 lanes of wave 0.  The
-// Gray-order walk over these prefix sums visits l ^ XOR_{bit j of i} B_j at
-// index i, since g^-1 maps y to its prefix parities (bit j = XOR of y_k,
-// k >= j).  The caller synchronises the workgroup afterwards.
-__device__ __forceinline__ void prefix_xor_basis_w1(uint64_t *Bx, int r) {
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x;
-    uint64_t v = Bx[lane];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint64_t t = __shfl_up(v, d);
-        if (lane >= d) v ^= t;
-    }
-    if (lane < r) Bx[lane] = v;
-}
-
-template <typename T>
-__global__ __launch_bounds__(kTileThreads) void enum_tile_kernel(FactorIn f, uint64_t begin,
-                                                                 uint64_t count,
-                                                                 T *__restrict__ out,
-                                                                 uint64_t tiles_per_block,
-                                                                 int counter) {
-    constexpr int S = tile_shift<T>();
-    __shared__ uint64_t Bx[64];
-    int r;
-    if (!gate(f, begin, count, r)) return;
-    load_basis_padded<1>(f.basis, r, Bx, threadIdx.x, blockDim.x);
-    __syncthreads();
-    if (counter) {
-        prefix_xor_basis_w1(Bx, r);
-        __syncthreads();
-    }
-    const uint64_t end = begin + count;
-    const uint64_t ntiles = ((end - 1) >> S) - (begin >> S) + 1;
-    const uint64_t t0 = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * tiles_per_block;
-    if (t0 >= ntiles) return;
-    const uint64_t t1 = (t0 + tiles_per_block < ntiles) ? t0 + tiles_per_block : ntiles;
-    enum_tiles_w1<T>(Bx, f.shift[0], begin, count, out, t0, t1);
+template <typename T, bool kCounter>
+__global__ __launch_bounds__(kVecThreads) void enum_tile_kernel(FactorIn f, VecRange g, uint32_t blocks,
+                                                                uint32_t tiles_per_block) {
+    const uint32_t t0 = xcd_block(blockIdx.x, blocks) * tiles_per_block;
+    const uint32_t t1 = t0 + tiles_per_block < g.ntiles ? t0 + tiles_per_block : g.ntiles;
+    vec_materialise<T, kCounter>(f.status, f.rank, f.basis, f.shift, f.n, g, t0, t1);
 }
 
 // ---------------------------------------------------------------------------
@@ -145,13 +113,13 @@ __global__ __launch_bounds__(kTileThreads) void enum_wide_tile_kernel(FactorIn f
 }
 
 // ---------------------------------------------------------------------------
-// General materialise: z_i = l ^ XOR_m Tab[m][digit m of i].
-// W = 1: 8 byte tables of 256 entries (16 KiB); W > 1: 16 nibble tables of
-// 16 entries, W words each (<= 32 KiB).
+// W > 1 words at an address that is not a multiple of 8, and the reduce of
+// W > 3: z_i = l ^ XOR_m Tab[m][digit m of i], 16 nibble tables of 16 entries
+// of W words (<= 32 KiB).
 // ---------------------------------------------------------------------------
 template <int WMAX>
 struct GenTables {
-    static constexpr int kDigitBits = (WMAX == 1) ? 8 : 4;
+    static constexpr int kDigitBits = 4;
     static constexpr int kDigits = 64 / kDigitBits;
     static constexpr int kEntries = 1 << kDigitBits;
     uint64_t tab[kDigits * kEntries * WMAX];
@@ -182,10 +150,9 @@ __device__ int build_tables(const FactorIn &f, int r, int W, bool counter, GenTa
     return ndig;
 }
 
-template <int WMAX, typename T>
-__global__ __launch_bounds__(256) void enum_general_kernel(FactorIn f, uint64_t begin,
-                                                           uint64_t count, T *__restrict__ out,
-                                                           int counter) {
+template <int WMAX>
+__global__ __launch_bounds__(256) void enum_general_kernel(FactorIn f, uint64_t begin, uint64_t count,
+                                                           uint64_t *__restrict__ out, int counter) {
     using G = GenTables<WMAX>;
     __shared__ G g;
     int r;
@@ -193,32 +160,19 @@ __global__ __launch_bounds__(256) void enum_general_kernel(FactorIn f, uint64_t 
     const int W = f.words;
     const int ndig = build_tables<WMAX>(f, r, W, counter != 0, g);
     __syncthreads();
-    if constexpr (WMAX == 1) {
-        const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-        for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < count; j += stride) {
-            const uint64_t i = begin + j;
-            uint64_t z = g.l[0];
-            for (int m = 0; m < ndig; ++m) {
-                const int d = (int)((i >> (m * G::kDigitBits)) & (G::kEntries - 1));
-                z ^= g.tab[m * G::kEntries + d];
-            }
-            out[j] = (T)z;
+    // WMAX lanes per solution, lane w computes and stores word w: the
+    // active lanes of a wave store one contiguous run of words.
+    const int w = (int)(threadIdx.x & (WMAX - 1));
+    const uint64_t stride = ((uint64_t)gridDim.x * blockDim.x) / WMAX;
+    for (uint64_t j = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WMAX; j < count;
+         j += stride) {
+        const uint64_t i = begin + j;
+        uint64_t z = (w < W) ? g.l[w] : 0ull;
+        for (int m = 0; m < ndig; ++m) {
+            const int d = (int)((i >> (m * G::kDigitBits)) & (G::kEntries - 1));
+            z ^= g.tab[(m * G::kEntries + d) * WMAX + w];
         }
-    } else {
-        // WMAX lanes per solution, lane w computes and stores word w: the
-        // active lanes of a wave store one contiguous run of words.
-        const int w = (int)(threadIdx.x & (WMAX - 1));
-        const uint64_t stride = ((uint64_t)gridDim.x * blockDim.x) / WMAX;
-        for (uint64_t j = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WMAX; j < count;
-             j += stride) {
-            const uint64_t i = begin + j;
-            uint64_t z = (w < W) ? g.l[w] : 0ull;
-            for (int m = 0; m < ndig; ++m) {
-                const int d = (int)((i >> (m * G::kDigitBits)) & (G::kEntries - 1));
-                z ^= g.tab[(m * G::kEntries + d) * WMAX + w];
-            }
-            if (w < W) out[j * W + w] = z;
-        }
+        if (w < W) out[j * W + w] = z;
     }
 }
 
@@ -235,103 +189,98 @@ __global__ __launch_bounds__(256) void enum_general_kernel(FactorIn f, uint64_t 
 // The scatter is linear in the bits of i, so R = R_lo(x) ^ R_hi(T) for
 // i = (T << S) | x; the circuit itself runs for every solution.
 // ---------------------------------------------------------------------------
+// One 16-byte store per thread and tile, as vec_materialise (stage2.h), with
+// the unit vectors of the pivots in the place of the basis rows: they give R.
+// The layers then run on every solution.  16-bit words go through them in
+// pairs, one in each half of a dword: no edge mask holds a bit whose shift
+// would leave its half.  allowH and allowV are the vertices that have a
+// right and a lower neighbour on the grid; every wave reads A's rows, takes
+// the edge masks from them by ballots and checks that A has no other entry.
+// Its set-up is some 40 vector instructions beside 50 per tile, so a
+// workgroup takes kCircuitTiles tiles.
+constexpr uint32_t kCircuitTiles = 2;
+
 template <typename T>
-__global__ __launch_bounds__(kTileThreads) void circuit_tile_kernel(
-    FactorIn f, const int32_t *__restrict__ pivots, const uint64_t *__restrict__ rows, int N,
-    uint64_t begin, uint64_t count, T *__restrict__ out, uint64_t tiles_per_block) {
-    constexpr int V = Vec<T>::V;
-    constexpr int S = tile_shift<T>();
-    __shared__ uint64_t PM[65];  // PM[k] = OR of e_{p_j}, j < min(k, r)
-    __shared__ uint64_t masks[3];
-    __shared__ int grid_ok;
-    int r;
-    if (!gate(f, begin, count, r)) return;
-    const int tid = threadIdx.x;
-    const int n = f.n;
-    if (tid < 64) {
-        const int v = tid;
-        const uint64_t row = (v < n) ? rows[v] : 0ull;
-        const int gr = v / N, gc = v - (v / N) * N;
-        uint64_t allowed = 0;
-        if (v < n) {
-            allowed |= 1ull << v;
-            if (gc > 0) allowed |= 1ull << (v - 1);
-            if (gc < N - 1) allowed |= 1ull << (v + 1);
-            if (gr > 0) allowed |= 1ull << (v - N);
-            if (gr < N - 1) allowed |= 1ull << (v + N);
-        }
-        const bool off_grid = (row & ~allowed) != 0;
-        const uint64_t H = __ballot(v < n && gc < N - 1 && ((row >> (v + 1)) & 1ull));
-        const uint64_t Vm = __ballot(v < n && gr < N - 1 && ((row >> (v + N)) & 1ull));
-        const uint64_t bb = __ballot(v < n && ((row >> v) & 1ull));
-        const bool any_off = __ballot(off_grid) != 0;
-        if (tid == 0) {
-            masks[0] = H;
-            masks[1] = Vm;
-            masks[2] = bb;
-            grid_ok = any_off ? 0 : 1;
-            uint64_t acc = 0;
-            PM[0] = 0;
-            for (int k = 0; k < 64; ++k) {
-                if (k < r) acc |= 1ull << pivots[k];
-                PM[k + 1] = acc;
-            }
-        }
+__global__ __launch_bounds__(kVecThreads) void circuit_tile_kernel(
+    FactorIn f, const int32_t *__restrict__ pivots, const uint64_t *__restrict__ rows, int N, uint64_t allowH,
+    uint64_t allowV, VecRange g, uint32_t blocks, uint32_t tiles_per_block) {
+    using X = VecTile<T>;
+    constexpr int V = X::V, LOGV = X::LOGV, ND = X::ND, LB = X::LB;
+    const uint32_t t0 = xcd_block(blockIdx.x, blocks) * tiles_per_block;
+    const uint32_t t1 = t0 + tiles_per_block < g.ntiles ? t0 + tiles_per_block : g.ntiles;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t n = (uint32_t)f.n;
+    const uint32_t own_row = lane < n ? lane : n - 1u;
+    const int32_t own_pivot = pivots[own_row];
+    uint64_t row = rows[own_row];
+    const int32_t st = *f.status, r = *f.rank;
+    const uint64_t l = f.shift[0];
+    // Pivots past r are -1: their bits of the index are never set.
+    int32_t p[LB];
+    if (f.n >= LB) {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) p[j] = pivots[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) p[j] = pivots[j < f.n ? j : f.n - 1];
     }
-    __syncthreads();
-    if (!grid_ok) {
+    asm volatile("" ::"s"(g.begin), "s"(g.end), "s"(g.tile0), "s"(g.full1), "s"(l), "s"(r), "s"(st), "s"(p[0]),
+                 "s"(t0), "s"(t1), "s"(allowH), "s"(allowV));
+    if (!vec_gate(f.status, st, r, g)) return;
+    row = lane < n ? row : 0ull;
+    // Row v turned right by v: bit 0 the colour, 1 and N the edges to v + 1
+    // and v + N, 63 and 64 - N those to v - 1 and v - N.
+    const uint64_t turned = (row >> lane) | (row << ((64u - lane) & 63u));
+    const uint64_t mH = __ballot((turned >> 1) & 1ull) & allowH, mV = __ballot((turned >> N) & 1ull) & allowV,
+                   mb = __ballot(turned & 1ull);
+    const bool left = __builtin_amdgcn_inverse_ballot_w64(allowH << 1), right = __builtin_amdgcn_inverse_ballot_w64(allowH);
+    const bool up = __builtin_amdgcn_inverse_ballot_w64(allowV << N), down = __builtin_amdgcn_inverse_ballot_w64(allowV);
+    const uint64_t ok = 1ull | (right ? 2ull : 0ull) | (down ? 1ull << N : 0ull) | (left ? 1ull << 63 : 0ull) |
+                        (up ? 1ull << (64 - N) : 0ull);
+    if (__ballot((turned & ~ok) != 0ull)) {
         if (tid == 0) *f.status = HLF_EINVAL;
         return;
     }
-    // The layers in the output width: n <= 32 bits fit one dword.
-    using U = typename std::conditional<sizeof(T) <= 4, uint32_t, uint64_t>::type;
-    const U H = (U)masks[0], Vm = (U)masks[1], bb = (U)masks[2];
-    const U l = (U)f.shift[0];
-    U Rlo[V];
+    uint64_t low[LB];
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-        const uint64_t x = (uint64_t)(tid * V + e);
-        U R = 0;
-        for (int j = 0; j < S; ++j)
-            if ((x >> j) & 1ull) R ^= (U)(PM[j + 1] ^ PM[j]);
-        Rlo[e] = R;
-    }
-    const uint64_t end = begin + count;
-    const uint64_t ntiles = ((end - 1) >> S) - (begin >> S) + 1;
-    const uint64_t t0 = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * tiles_per_block;
-    if (t0 >= ntiles) return;
-    const uint64_t t1 = (t0 + tiles_per_block < ntiles) ? t0 + tiles_per_block : ntiles;
-    uint64_t Tt = (begin >> S) + t0;
-    U Rhi = 0;
-    for (int j = 0; j + S < 64 && (Tt >> j); ++j)
-        if ((Tt >> j) & 1ull) Rhi ^= (U)(PM[S + j + 1] ^ PM[S + j]);
-    for (uint64_t t = t0; t < t1; ++t, ++Tt) {
-        uint64_t zv[V];
+    for (int j = 0; j < LB; ++j) low[j] = 1ull << (p[j] & 63);
+    uint32_t le[ND], ls[ND], lo[ND], pf[V][ND], H[ND], Vm[ND], bb[ND];
+    vec_dwords<T>(1ull << (own_pivot & 63), le);
+    vec_dwords<T>(l, ls);
+    vec_dwords<T>(mH, H);
+    vec_dwords<T>(mV, Vm);
+    vec_dwords<T>(mb, bb);
+    const uint32_t x = lane << LOGV;
+    vec_lane_part<T, true>(low, x, lo);
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            const U R = Rlo[e] ^ Rhi;
-            const U y = ((R & H) << 1) ^ ((R >> 1) & H) ^ ((R & Vm) << N) ^ ((R >> N) & Vm) ^ (R & bb);
-            zv[e] = (uint64_t)(U)(y ^ l);
-        }
-        const uint64_t i0 = (Tt << S) + (uint64_t)(tid * V);
-        if (i0 >= begin && i0 + V <= end) {
-            uint32_t w[4];
-            pack16<T>(zv, w);
-            u32x4 val;
-            val.x = w[0];
-            val.y = w[1];
-            val.z = w[2];
-            val.w = w[3];
-            __builtin_nontemporal_store(val, (u32x4 *)(out + (i0 - begin)));
+    for (int e = 0; e < V; ++e) vec_place<T, true>(low, e, pf[e]);
+    const uint64_t first = g.begin & ~((1ull << X::S) - 1);
+    for (uint32_t t = t0; t < t1; ++t) {
+        const uint64_t iu = first + ((uint64_t)t << X::S) + (wave << LB);
+        const bool on = __builtin_amdgcn_inverse_ballot_w64(iu);
+        uint32_t h[ND];
+#pragma unroll
+        for (int q = 0; q < ND; ++q) h[q] = on ? le[q] : 0u;
+        wave_xor_dwords<ND>(h);
+        uint32_t w[4];
+        vec_values<T>(lo, h, pf, w);  // R
+        if constexpr (ND == 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t R = w[k];
+                w[k] = ((R & H[0]) << 1) ^ ((R >> 1) & H[0]) ^ ((R & Vm[0]) << N) ^ ((R >> N) & Vm[0]) ^ (R & bb[0]) ^ ls[0];
+            }
         } else {
 #pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const uint64_t i = i0 + e;
-                if (i >= begin && i < end) out[i - begin] = (T)zv[e];
+            for (int k = 0; k < 4; k += 2) {
+                const uint64_t R = ((uint64_t)w[k + 1] << 32) | w[k];
+                const uint64_t y = ((R & mH) << 1) ^ ((R >> 1) & mH) ^ ((R & mV) << N) ^ ((R >> N) & mV) ^ (R & mb) ^ l;
+                w[k] = (uint32_t)y;
+                w[k + 1] = (uint32_t)(y >> 32);
             }
         }
-        const int c = S + __builtin_ctzll(Tt + 1) + 1;
-        Rhi ^= (U)(PM[c < 64 ? c : 64] ^ PM[S]);
+        vec_put<T>(g, t, iu + x, w);
     }
 }
 
@@ -494,18 +443,13 @@ uint64_t tiles_per_block_for(uint64_t ntiles, uint64_t tile_bytes, uint64_t *blo
 template <typename T>
 hlf_status launch_tile(const FactorIn &f, uint64_t begin, uint64_t count, T *out, int counter,
                        hipStream_t stream) {
-    constexpr int S = tile_shift<T>();
-    const uint64_t end = begin + count;  // host: may wrap only for invalid ranges
-    uint64_t ntiles;
-    if (end < begin) {
-        ntiles = 1;  // invalid range: the device gate reports HLF_ERANGE
-    } else {
-        ntiles = ((end - 1) >> S) - (begin >> S) + 1;
-    }
-    uint64_t blocks;
-    const uint64_t tpb = tiles_per_block_for(ntiles, kTileBytes, &blocks);
-    hipLaunchKernelGGL(enum_tile_kernel<T>, dim3((unsigned)blocks), dim3(kTileThreads), 0, stream,
-                       f, begin, count, out, tpb, counter);
+    const VecRange g = vec_range<T>(begin, count, out);
+    const uint32_t tpb = vec_tiles_per_block(g.ntiles);
+    const uint32_t blocks = g.ntiles ? (g.ntiles + tpb - 1) / tpb : 1u;
+    if (counter)
+        hipLaunchKernelGGL((enum_tile_kernel<T, true>), dim3(blocks), dim3(kVecThreads), 0, stream, f, g, blocks, tpb);
+    else
+        hipLaunchKernelGGL((enum_tile_kernel<T, false>), dim3(blocks), dim3(kVecThreads), 0, stream, f, g, blocks, tpb);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
@@ -527,15 +471,15 @@ hlf_status launch_wide_tile(const FactorIn &f, uint64_t begin, uint64_t count, u
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
-template <int WMAX, typename T>
-hlf_status launch_general(const FactorIn &f, uint64_t begin, uint64_t count, T *out, int counter,
+template <int WMAX>
+hlf_status launch_general(const FactorIn &f, uint64_t begin, uint64_t count, uint64_t *out, int counter,
                           hipStream_t stream) {
     const uint64_t per_block = 256 / WMAX;  // solutions per workgroup pass
     uint64_t blocks = (count + per_block - 1) / per_block;
     const uint64_t cap = (uint64_t)device_cu_count() * 8;
     if (blocks > cap) blocks = cap;
     if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL((enum_general_kernel<WMAX, T>), dim3((unsigned)blocks), dim3(256), 0,
+    hipLaunchKernelGGL(enum_general_kernel<WMAX>, dim3((unsigned)blocks), dim3(256), 0,
                        stream, f, begin, count, out, counter);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
@@ -574,21 +518,10 @@ hlf_status launch_enumerate(const FactorIn &f, uint64_t begin, uint64_t count, i
                             bool counter_order, void *out, hipStream_t stream) {
     const int W = f.words;
     const int c = counter_order ? 1 : 0;
-    const bool aligned16 = ((uintptr_t)out & 15u) == 0;
     if (W == 1 && word_bits <= 64) {
-        if (word_bits == 16) {
-            if (aligned16 && begin % Vec<uint16_t>::V == 0)
-                return launch_tile<uint16_t>(f, begin, count, (uint16_t *)out, c, stream);
-            return launch_general<1, uint16_t>(f, begin, count, (uint16_t *)out, c, stream);
-        }
-        if (word_bits == 32) {
-            if (aligned16 && begin % Vec<uint32_t>::V == 0)
-                return launch_tile<uint32_t>(f, begin, count, (uint32_t *)out, c, stream);
-            return launch_general<1, uint32_t>(f, begin, count, (uint32_t *)out, c, stream);
-        }
-        if (aligned16 && begin % Vec<uint64_t>::V == 0)
-            return launch_tile<uint64_t>(f, begin, count, (uint64_t *)out, c, stream);
-        return launch_general<1, uint64_t>(f, begin, count, (uint64_t *)out, c, stream);
+        if (word_bits == 16) return launch_tile<uint16_t>(f, begin, count, (uint16_t *)out, c, stream);
+        if (word_bits == 32) return launch_tile<uint32_t>(f, begin, count, (uint32_t *)out, c, stream);
+        return launch_tile<uint64_t>(f, begin, count, (uint64_t *)out, c, stream);
     }
     uint64_t *o = (uint64_t *)out;
     if (((uintptr_t)out & 7u) == 0) {
@@ -597,10 +530,10 @@ hlf_status launch_enumerate(const FactorIn &f, uint64_t begin, uint64_t count, i
         if (W <= 8) return launch_wide_tile<8>(f, begin, count, o, c, stream);
         return launch_wide_tile<16>(f, begin, count, o, c, stream);
     }
-    if (W <= 2) return launch_general<2, uint64_t>(f, begin, count, o, c, stream);
-    if (W <= 4) return launch_general<4, uint64_t>(f, begin, count, o, c, stream);
-    if (W <= 8) return launch_general<8, uint64_t>(f, begin, count, o, c, stream);
-    return launch_general<16, uint64_t>(f, begin, count, o, c, stream);
+    if (W <= 2) return launch_general<2>(f, begin, count, o, c, stream);
+    if (W <= 4) return launch_general<4>(f, begin, count, o, c, stream);
+    if (W <= 8) return launch_general<8>(f, begin, count, o, c, stream);
+    return launch_general<16>(f, begin, count, o, c, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -760,12 +693,16 @@ hlf_status launch_circuit(const FactorIn &f, const int32_t *pivots, const uint64
     const uint64_t end = begin + count;
     auto go = [&](auto tag) -> hlf_status {
         using T = decltype(tag);
-        constexpr int S = tile_shift<T>();
-        const uint64_t ntiles = (end < begin) ? 1 : ((end - 1) >> S) - (begin >> S) + 1;
-        uint64_t blocks;
-        const uint64_t tpb = tiles_per_block_for(ntiles, kTileBytes, &blocks);
-        hipLaunchKernelGGL(circuit_tile_kernel<T>, dim3((unsigned)blocks), dim3(kTileThreads), 0,
-                           stream, f, pivots, rows, N, begin, count, (T *)out, tpb);
+        const VecRange g = vec_range<T>(begin, count, out);
+        uint64_t allowH = 0, allowV = 0;
+        for (int v = 0; v < f.n; ++v) {
+            if (v % N < N - 1) allowH |= 1ull << v;
+            if (v + N < f.n) allowV |= 1ull << v;
+        }
+        const uint32_t tpb = std::max(kCircuitTiles, vec_tiles_per_block(g.ntiles));
+        const uint32_t blocks = g.ntiles ? (g.ntiles + tpb - 1) / tpb : 1u;
+        hipLaunchKernelGGL(circuit_tile_kernel<T>, dim3(blocks), dim3(kVecThreads), 0, stream, f, pivots, rows, N,
+                           allowH, allowV, g, blocks, tpb);
         return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
     };
     if (word_bits == 16) return go(uint16_t{});

@@ -226,6 +226,248 @@ __device__ void enum_tiles_w1(const uint64_t *Bx, uint64_t l, uint64_t begin, ui
 }
 
 // ---------------------------------------------------------------------------
+// Materialise, one 16-byte store per thread (the kernels that only write).
+//
+// Bound by HBM writes, and what decides their rate here is the order in which
+// the addresses are written.  Plain store kernels on this card: one store per
+// thread and 4 KiB per 256-thread workgroup 6.9 TB/s (512 MiB and 1 GiB), two
+// stores per thread 6.6, four 6.0, 128 KiB per 1024-thread workgroup 5.7,
+// resident workgroups that stride over the range at most 6.2, and nontemporal
+// stores 2-4% below plain ones (15% at 128 MiB).  So a workgroup writes one
+// tile of 4 KiB, and the set-up of a wave has to fit beside it: at that rate
+// a SIMD starts a wave every 350 cycles, about 85 scalar and as many vector
+// instructions, and holds at most eight.  Solution i is l ^ XOR of the B_j
+// over the bits j of c(i), c(i) = i ^ (i >> 1) in Gray order and i in counter
+// order, both linear.  A wave takes no LDS and no barrier: the rows for the
+// index bits inside its run of 64 V solutions are scalar loads, applied per
+// lane under the lane's bits; the others are loaded one per lane, kept where
+// c of the run's first index has that bit (the mask is the select), and XORed
+// across the wave by DPP.
+//
+// A run that begins anywhere is cut at multiples of V by index, so its
+// 16-byte stores may be misaligned in memory, which costs nothing measurable
+// as long as each XCD writes one contiguous run (xcd_block): dealt in turn,
+// misaligned tiles straddle two XCDs' pages and drop to 4.8 TB/s.
+// ---------------------------------------------------------------------------
+constexpr int kVecThreads = 256;
+constexpr int kLogVecThreads = 8;
+// A launch has at most 2^31 threads; longer ranges take more tiles each.
+constexpr uint64_t kMaxVecBlocks = 1ull << 23;
+
+typedef u32x4 u32x4_any __attribute__((aligned(1)));  // a 16-byte store at any address
+
+template <typename T>
+struct VecTile {
+    static constexpr int V = Vec<T>::V;
+    static constexpr int LOGV = Vec<T>::LOGV;
+    static constexpr int ND = sizeof(T) == 8 ? 2 : 1;        // dwords per constant
+    static constexpr int LB = LOGV + 6;                      // index bits inside a wave's run
+    static constexpr int S = LOGV + kLogVecThreads;          // log2 solutions per tile
+};
+
+// Where a range of solutions goes, worked out on the host.
+struct VecRange {
+    uint64_t begin, end;      // indices; end < begin for a range that wraps
+    char *tile0;              // address of tile 0's first index (at or before the output)
+    uint32_t ntiles;          // 0: nothing but the device gate (see vec_range)
+    uint32_t full0, full1;    // tiles full0 <= t < full1 lie inside the range
+};
+
+// ntiles is 0 for a range that wraps, or that no memory holds (2^31 tiles are
+// 8 TiB): the launch then runs the gate alone.
+template <typename T>
+inline VecRange vec_range(uint64_t begin, uint64_t count, void *out) {
+    constexpr int S = VecTile<T>::S;
+    constexpr uint64_t M = (1ull << S) - 1;
+    VecRange g{};
+    g.begin = begin;
+    g.end = begin + count;
+    g.tile0 = static_cast<char *>(out) - (begin & M) * sizeof(T);
+    if (count == 0 || g.end < begin) return g;
+    const uint64_t t = ((g.end - 1) >> S) - (begin >> S) + 1;
+    if (t >> 31) return g;
+    g.ntiles = (uint32_t)t;
+    g.full0 = (begin & M) ? 1u : 0u;
+    g.full1 = (uint32_t)((g.end - (begin & ~M)) >> S);
+    return g;
+}
+
+// Tiles per workgroup for ntiles tiles: 1 up to kMaxVecBlocks of them.
+inline uint32_t vec_tiles_per_block(uint64_t ntiles) {
+    return ntiles ? (uint32_t)((ntiles + kMaxVecBlocks - 1) / kMaxVecBlocks) : 1u;
+}
+
+// A word as the dwords that the stores are made of (16-bit words twice).
+template <typename T>
+__device__ __forceinline__ void vec_dwords(uint64_t e, uint32_t (&d)[VecTile<T>::ND]) {
+    if constexpr (sizeof(T) == 8) {
+        d[0] = (uint32_t)e;
+        d[1] = (uint32_t)(e >> 32);
+    } else if constexpr (sizeof(T) == 4) {
+        d[0] = (uint32_t)e;
+    } else {
+        d[0] = (uint32_t)(e & 0xFFFFu) * 0x10001u;
+    }
+}
+
+// XOR of the wave's values, wave-uniform, by DPP row shifts and a row
+// broadcast.  A pair of dwords first folds onto one register: one swap of the
+// lane halves leaves the low dwords' XORs in lanes 0..31 and the high ones'
+// in lanes 32..63.
+__device__ __forceinline__ uint32_t dpp_half_xor(uint32_t v) {
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);  // row_shr 1, 2, 4, 8
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // lane 15 to the next row
+    return v;  // lanes 31 and 63: the XORs of their halves
+}
+
+template <int ND>
+__device__ __forceinline__ void wave_xor_dwords(uint32_t (&d)[ND]) {
+    if constexpr (ND == 1) {
+        const uint32_t v = dpp_half_xor(d[0]);
+        d[0] = (uint32_t)__builtin_amdgcn_readlane((int)v, 31) ^ (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    } else {
+        const auto sw = __builtin_amdgcn_permlane32_swap(d[0], d[1], false, false);
+        const uint32_t v = dpp_half_xor(sw[0] ^ sw[1]);
+        d[0] = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
+        d[1] = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    }
+}
+
+// This thread's V solutions i0 .. i0 + V - 1 of tile t, as dwords w.
+template <typename T>
+__device__ __forceinline__ void vec_put(const VecRange &g, uint32_t t, uint64_t i0, const uint32_t (&w)[4]) {
+    char *base = g.tile0 + ((uint64_t)t << 12);
+    const uint32_t off = 16u * threadIdx.x;
+    if (t >= g.full0 && t < g.full1) {  // workgroup-uniform
+        const u32x4 val = {w[0], w[1], w[2], w[3]};
+        *reinterpret_cast<u32x4_any *>(base + off) = val;
+    } else {
+        T *o = reinterpret_cast<T *>(base + off);
+#pragma unroll
+        for (int e = 0; e < VecTile<T>::V; ++e) {
+            if (i0 + e >= g.begin && i0 + e < g.end) {
+                if constexpr (sizeof(T) == 2) o[e] = (T)(w[e >> 1] >> (16 * (e & 1)));
+                else if constexpr (sizeof(T) == 4) o[e] = (T)w[e];
+                else o[e] = ((uint64_t)w[2 * e + 1] << 32) | w[2 * e];
+            }
+        }
+    }
+}
+
+// Lane part of a linear map of the index: XOR of the rows low[j] over the bits
+// j < LB of c(lane * V) (see above; bit LOGV + 5 of c also takes bit LOGV + 6
+// of the index, which is in the run's constant).
+template <typename T, bool kCounter>
+__device__ __forceinline__ void vec_lane_part(const uint64_t (&low)[VecTile<T>::LB], uint32_t x,
+                                              uint32_t (&lo)[VecTile<T>::ND]) {
+    constexpr int LOGV = VecTile<T>::LOGV, ND = VecTile<T>::ND;
+    constexpr int J0 = kCounter ? LOGV : LOGV - 1;
+    const uint32_t cx = kCounter ? x : x ^ (x >> 1);
+#pragma unroll
+    for (int j = J0; j < VecTile<T>::LB; ++j) {
+        const uint32_t m = (uint32_t)((int)(cx << (31 - j)) >> 31);
+        uint32_t e[ND];
+        vec_dwords<T>(low[j], e);
+#pragma unroll
+        for (int q = 0; q < ND; ++q)  // lo ^ (m & e)
+            lo[q] = j == J0 ? m & e[q] : __builtin_amdgcn_bitop3_b32(lo[q], m, e[q], 0x78);
+    }
+}
+
+// F(e) for a value's place e < V within the store.
+template <typename T, bool kCounter>
+__device__ __forceinline__ void vec_place(const uint64_t (&low)[VecTile<T>::LB], int e,
+                                          uint32_t (&f)[VecTile<T>::ND]) {
+    const int c = kCounter ? e : e ^ (e >> 1);
+    uint64_t v = 0;
+#pragma unroll
+    for (int j = 0; j < VecTile<T>::LOGV; ++j)
+        if ((c >> j) & 1) v ^= low[j];
+    vec_dwords<T>(v, f);
+}
+
+// The V values of a store: lane part, run constant and places together.
+template <typename T>
+__device__ __forceinline__ void vec_values(const uint32_t (&lo)[VecTile<T>::ND], const uint32_t (&h)[VecTile<T>::ND],
+                                           const uint32_t (&f)[VecTile<T>::V][VecTile<T>::ND], uint32_t (&w)[4]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if constexpr (sizeof(T) == 2)
+            w[k] = lo[0] ^ (h[0] ^ ((f[2 * k][0] & 0xFFFFu) | (f[2 * k + 1][0] & 0xFFFF0000u)));
+        else if constexpr (sizeof(T) == 4)
+            w[k] = lo[0] ^ (h[0] ^ f[k][0]);
+        else
+            w[k] = lo[k & 1] ^ (h[k & 1] ^ f[k >> 1][k & 1]);
+    }
+}
+
+// The gate on a record, for kernels that read it with plain loads: the rank r
+// of a good record and a range inside [0, 2^r).
+__device__ __forceinline__ bool vec_gate(int32_t *status, int32_t st, int32_t r, const VecRange &g) {
+    if (st != HLF_OK) return false;
+    if (r > HLF_MAX_ENUM_RANK || g.end < g.begin || (g.end - 1) >> r) {
+        if (threadIdx.x == 0) *status = HLF_ERANGE;
+        return false;
+    }
+    return true;
+}
+
+// Tiles [t0, t1) of a range, one store per thread and tile.  The basis array
+// has n rows, all loaded at once with the status and the rank: rows past r
+// meet no bit (indices are below 2^r, and so is c of them).
+template <typename T, bool kCounter>
+__device__ __forceinline__ void vec_materialise(int32_t *status, const int32_t *__restrict__ rank,
+                                                const uint64_t *__restrict__ basis,
+                                                const uint64_t *__restrict__ shift, int n, const VecRange &g,
+                                                uint32_t t0, uint32_t t1) {
+    using X = VecTile<T>;
+    constexpr int V = X::V, LOGV = X::LOGV, ND = X::ND, LB = X::LB;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t rows = (uint32_t)n;
+    const uint64_t own = basis[lane < rows ? lane : rows - 1u];
+    const int32_t st = *status, r = *rank;
+    const uint64_t l = shift[0];
+    uint64_t low[LB];
+    if (n >= LB) {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) low[j] = basis[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) low[j] = basis[j < n ? j : n - 1];
+    }
+    // Every load is under way before the first branch on one of them.
+    asm volatile("" ::"s"(g.begin), "s"(g.end), "s"(g.tile0), "s"(g.full1), "s"(l), "s"(r), "s"(st), "s"(low[0]),
+                 "s"(t0), "s"(t1));
+    if (!vec_gate(status, st, r, g)) return;
+    uint32_t le[ND], ls[ND], lo[ND], f[V][ND];
+    vec_dwords<T>(own, le);
+    vec_dwords<T>(l, ls);
+    const uint32_t x = lane << LOGV;
+    vec_lane_part<T, kCounter>(low, x, lo);
+#pragma unroll
+    for (int e = 0; e < V; ++e) vec_place<T, kCounter>(low, e, f[e]);
+    const uint64_t first = g.begin & ~((1ull << X::S) - 1);
+    for (uint32_t t = t0; t < t1; ++t) {
+        // the wave's run begins at index iu: its constant l ^ F(iu)
+        const uint64_t iu = first + ((uint64_t)t << X::S) + (wave << LB);
+        const bool on = __builtin_amdgcn_inverse_ballot_w64(kCounter ? iu : iu ^ (iu >> 1));
+        uint32_t h[ND];
+#pragma unroll
+        for (int q = 0; q < ND; ++q) h[q] = on ? le[q] : 0u;
+        wave_xor_dwords<ND>(h);
+#pragma unroll
+        for (int q = 0; q < ND; ++q) h[q] ^= ls[q];
+        uint32_t w[4];
+        vec_values<T>(lo, h, f, w);
+        vec_put<T>(g, t, iu + x, w);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Reduce on one wavefront, W = WW words (n <= 64*WW).  Tiles of 64*U indices.
 // ---------------------------------------------------------------------------
 template <int WW>
