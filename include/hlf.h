@@ -299,7 +299,7 @@ typedef struct hlf_batch_layout {
 } hlf_batch_layout;
 
 /* Launch parameters of hlf_batch_reduce: chunks of 2^chunk_log2 solutions
- * (10..30) are the unit of dynamic scheduling; waves_per_cu (1..16) sizes the
+ * (10..30) are the largest unit of dynamic scheduling; waves_per_cu (1..16) sizes the
  * persistent grid.  hlf_batch_tune picks both by timing the real batch.       */
 typedef struct hlf_batch_params {
     int32_t chunk_log2;

@@ -13,7 +13,7 @@
 //                               both its slot and its first chunk, writes the
 //                               slot and releases it; wavefronts then take chunk
 //                               indices from a second counter and find the slot
-//                               by binary search.  A wave only waits for a slot
+//                               by 64-way search.  A wave only waits for a slot
 //                               that was already claimed (its writer is running)
 //                               or for factor tasks that running waves hold, so
 //                               every wait ends and the grid drains.
@@ -267,17 +267,21 @@ __global__ __launch_bounds__(kTileThreads) void batch_solve_kernel(BatchDev b,
 constexpr int kClaimShift = 40;  // claim word: (slots << 40) | chunks
 constexpr unsigned long long kChunkMask = (1ull << kClaimShift) - 1;
 
+// The drawn counters and the polled words lie on cache lines of their own.
 struct QueueHead {
-    unsigned int fnext;        // next factor task
-    unsigned int fdone;        // factor tasks finished
-    unsigned long long cnext;  // next chunk index
     unsigned long long claim;  // published slots and chunks
+    unsigned int fdone;        // factor tasks finished
+    char pad0[128 - 12];
+    unsigned int fnext;        // next factor task
+    char pad1[64 - 4];
+    unsigned long long cnext;  // next chunk index past the first gridDim.x
 };
 
+// One word per slot, zero until published: (first chunk + 1) << kInstBits |
+// instance.  First chunks are below 2^40, instances below 2^20.
+constexpr int kInstBits = 20;
 struct ChunkSlot {
-    unsigned long long base;  // first chunk index of the instance
-    int inst;
-    int ready;
+    unsigned long long entry;
 };
 
 __global__ void batch_queue_reset_kernel(QueueHead *q, ChunkSlot *slots, int count) {
@@ -288,11 +292,7 @@ __global__ void batch_queue_reset_kernel(QueueHead *q, ChunkSlot *slots, int cou
         q->cnext = 0;
         q->claim = 0;
     }
-    if (t < count) {
-        slots[t].base = 0;
-        slots[t].inst = 0;
-        slots[t].ready = 0;
-    }
+    if (t < count) slots[t].entry = 0;
 }
 
 // Offsets of the batch layout (prefix sums over the instance sizes) for the
@@ -350,43 +350,48 @@ __global__ __launch_bounds__(1024) void noalloc_layout_kernel(const int32_t *__r
     }
 }
 
-__device__ __forceinline__ unsigned long long slot_base(ChunkSlot *slots, int s) {
-    while (__builtin_amdgcn_readfirstlane(
-               __hip_atomic_load(&slots[s].ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT)) == 0)
-        __builtin_amdgcn_s_sleep(2);
-    return uniform64(__hip_atomic_load(&slots[s].base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+template <typename V>
+__device__ __forceinline__ V relaxed_load(const V *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Last slot whose first chunk is <= c (slot bases increase with the slot).
-__device__ int find_slot(ChunkSlot *slots, int nslots, unsigned long long c) {
-    int lo = 0, hi = nslots - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (slot_base(slots, mid) <= c) lo = mid; else hi = mid - 1;
-    }
-    (void)slot_base(slots, lo);
-    return lo;
-}
-
-template <int WW, int WMAX>
-__device__ void reduce_chunk(const BatchDev &b, int inst, int n, int r, unsigned long long c0,
-                             unsigned long long c1, uint64_t *Bx) {
+// Entry of the last of nslots claimed slots whose first chunk is <= c (first
+// chunks increase with the slot, slot 0's is 0).  64 slots are read at a time,
+// one per lane, evenly over what is left: two rounds for 4096 slots.  A claimed
+// slot that is still zero is about to be written by a running wave.
+__device__ __forceinline__ unsigned long long find_slot(const ChunkSlot *slots, int nslots, unsigned long long c) {
     const int lane = lane_id();
-    load_basis_padded<WW>(b.basis + b.mat_off[inst], r, Bx, lane, 64);
+    int lo = 0, len = nslots;
+    for (;;) {
+        const int step = (len + 63) >> 6;
+        const bool in = lane * step < len;
+        unsigned long long e = 0;
+        for (;;) {
+            if (in && e == 0) e = relaxed_load(&slots[lo + lane * step].entry);
+            if (__ballot(in && e == 0) == 0) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        const unsigned long long below = __ballot(in && (e >> kInstBits) - 1 <= c);  // lane 0 always
+        const int k = 63 - __builtin_clzll(below);
+        if (step == 1) return readlane64(e, k);
+        lo += k * step;
+        len = min(step, len - k * step);
+    }
+}
+
+template <int WW>
+__device__ void reduce_chunk(const BatchDev &b, int inst, int r, unsigned long long c0, unsigned long long c1) {
+    const WaveRows<WW> rows = wave_rows<WW>(b.basis + b.mat_off[inst], r);
     uint64_t l[WW];
     const uint64_t *sh = b.shift + b.vec_off[inst];
 #pragma unroll
-    for (int w = 0; w < WW; ++w) l[w] = sh[w];
-    __syncthreads();
-    const WavePartial<WW> p = wave_reduce_range<WW>(Bx, l, n, r, c0, c1);
-    uint64_t *cnt = b.counts + b.piv_off[inst];
+    for (int w = 0; w < WW; ++w) l[w] = uniform64(sh[w]);
+    const uint64_t acc = wave_sum_u64(wave_hash_range<WW>(rows, l, uniform64(c0), uniform64(c1),
+                                                          [&](int k, uint64_t(&row)[WW]) {
 #pragma unroll
-    for (int w = 0; w < WW; ++w) {
-        const int j = 64 * w + lane;
-        if (j < n && p.cnt[w]) atomicAdd((unsigned long long *)&cnt[j], (unsigned long long)p.cnt[w]);
-    }
-    if (lane == 0 && p.hash) atomicAdd((unsigned long long *)&b.hash[inst], (unsigned long long)p.hash);
-    __syncthreads();  // Bx is reused by the next chunk
+                                                              for (int w = 0; w < WW; ++w) row[w] = row_word<WW>(rows, k, w);
+                                                          }));
+    if (lane_id() == 0 && acc) atomicAdd((unsigned long long *)&b.hash[inst], (unsigned long long)acc);
 }
 
 template <int WMAX>
@@ -394,7 +399,6 @@ __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint
                                                           int max_rank, int chunk_log2,
                                                           QueueHead *q, ChunkSlot *slots) {
     __shared__ WaveSmem<WMAX> sm;
-    __shared__ uint64_t Bx[64 * WMAX];
     const int lane = lane_id();
 
     // Phase 1: factor tasks.
@@ -414,66 +418,75 @@ __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint
             *out.rank = 0;
             *out.status = HLF_EINVAL;
         }
+        // Counts over all 2^r solutions: half of them where row j of A (and so
+        // bit j of some B_k) is not zero; elsewhere none, since then A e_j = 0
+        // and q(e_j) = A_jj = 0 give l_j = 0.
         uint64_t *cnt = b.counts + b.piv_off[f];
-        for (int j = lane; j < n; j += 64) cnt[j] = 0;
-        if (lane == 0) b.hash[f] = 0;
-        __threadfence();  // the record and the zeroed results precede publication
-        if (lane == 0) {
-            if (r >= 0 && r <= max_rank) {
-                const unsigned long long nch =
-                    (r > chunk_log2) ? (1ull << (r - chunk_log2)) : 1ull;
-                const unsigned long long old =
-                    atomicAdd(&q->claim, (1ull << kClaimShift) | nch);
-                const int s = (int)(old >> kClaimShift);
-                slots[s].base = old & kChunkMask;
-                slots[s].inst = (int)f;
-                __hip_atomic_store(&slots[s].ready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            __hip_atomic_fetch_add(&q->fdone, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t half = r >= 1 && r <= max_rank ? 1ull << (r - 1) : 0ull;
+        for (int j = lane; j < n; j += 64) {
+            uint64_t any = 0;
+            if (half)
+                for (int w = 0; w < W; ++w) any |= sm.orig[j * W + w];
+            cnt[j] = any ? half : 0ull;
         }
+        if (lane == 0) b.hash[f] = 0;
+        if (r >= 0 && r <= max_rank) {  // wave-uniform
+            // The release makes the record and the zeroed hash visible to
+            // whoever reads the entry.
+            if (lane == 0) {
+                const unsigned long long nch = r > chunk_log2 ? 1ull << (r - chunk_log2) : 1ull;
+                const unsigned long long old = atomicAdd(&q->claim, (1ull << kClaimShift) | nch);
+                __hip_atomic_store(&slots[old >> kClaimShift].entry,
+                                   (((old & kChunkMask) + 1) << kInstBits) | (unsigned long long)f, __ATOMIC_RELEASE,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        // The claim has returned, so whoever reads this count reads it too.
+        if (lane == 0) __hip_atomic_fetch_add(&q->fdone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();  // LDS is reused by the next factor task
     }
 
-    // Phase 2: chunk tasks.
+    // Phase 2: chunk tasks, the first one by the wave's index.
+    unsigned long long c = blockIdx.x;
     for (;;) {
-        unsigned long long c = 0;
-        if (lane == 0) c = atomicAdd(&q->cnext, 1ull);
-        c = uniform64(c);
-        int s = -1;
-        for (;;) {
-            const unsigned long long cl = uniform64(
-                __hip_atomic_load(&q->claim, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT));
+        unsigned long long e = 0;
+        for (int naps = 0;; ++naps) {
+            const unsigned long long cl = uniform64(relaxed_load(&q->claim));
             if (c < (cl & kChunkMask)) {
-                s = find_slot(slots, (int)(cl >> kClaimShift), c);
+                e = find_slot(slots, (int)(cl >> kClaimShift), c);
                 break;
             }
-            const unsigned int done = (unsigned int)__builtin_amdgcn_readfirstlane((int)
-                __hip_atomic_load(&q->fdone, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT));
+            const unsigned int done = (unsigned int)__builtin_amdgcn_readfirstlane((int)relaxed_load(&q->fdone));
             if (done >= (unsigned int)b.count) {
-                // every claim happened before its fdone increment
-                const unsigned long long cl2 = uniform64(
-                    __hip_atomic_load(&q->claim, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT));
-                if (c < (cl2 & kChunkMask)) continue;
+                // every claim came before its task was counted
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (c < (uniform64(relaxed_load(&q->claim)) & kChunkMask)) continue;
                 break;
             }
-            __builtin_amdgcn_s_sleep(4);
+            // Thousands of waves polling at full rate hold up the atomics that
+            // they wait for: back off to 7 us.
+            if (naps < 4) __builtin_amdgcn_s_sleep(16);
+            else __builtin_amdgcn_s_sleep(127), __builtin_amdgcn_s_sleep(127);
         }
-        if (s < 0) break;
-        const int inst = __builtin_amdgcn_readfirstlane(
-            __hip_atomic_load(&slots[s].inst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        const unsigned long long local = c - slot_base(slots, s);
+        if (e == 0) break;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the record behind the entry
+        const int inst = (int)(e & ((1u << kInstBits) - 1));
+        const unsigned long long local = c - ((e >> kInstBits) - 1);
         const int n = b.n[inst];
         const int W = (n + 63) >> 6;
-        const int r = b.rank[inst];
+        const int r = __builtin_amdgcn_readfirstlane(b.rank[inst]);
         const unsigned long long total = 1ull << r;
         const unsigned long long c0 = local << chunk_log2;
         unsigned long long c1 = c0 + (1ull << chunk_log2);
         if (c1 > total) c1 = total;
-        if (W == 1) reduce_chunk<1, WMAX>(b, inst, n, r, c0, c1, Bx);
+        if (W == 1) reduce_chunk<1>(b, inst, r, c0, c1);
         if constexpr (WMAX >= 2)
-            if (W == 2) reduce_chunk<2, WMAX>(b, inst, n, r, c0, c1, Bx);
+            if (W == 2) reduce_chunk<2>(b, inst, r, c0, c1);
         if constexpr (WMAX >= 3)
-            if (W == 3) reduce_chunk<3, WMAX>(b, inst, n, r, c0, c1, Bx);
+            if (W == 3) reduce_chunk<3>(b, inst, r, c0, c1);
+        unsigned long long next = 0;
+        if (lane == 0) next = atomicAdd(&q->cnext, 1ull);
+        c = gridDim.x + uniform64(next);
     }
 }
 
@@ -570,6 +583,19 @@ bool claims_fit_count(int count, int max_rank, int chunk_log2) {
     return (unsigned long long)count < ((1ull << hlf::kClaimShift) / per);
 }
 
+// The pieces that a chunk is drawn in: 2^17 solutions, as far as the queue
+// counts that many.  A wave takes 0.6 ms for 2^20 solutions beside another on
+// its SIMD, and the last ones run while the rest of the card is idle (4096
+// grids at chunk_log2 20, 8 waves per CU: 6.51 ms in whole chunks, 6.19 in
+// pieces of 2^17, 6.27 of 2^16, 6.49 of 2^15, where the draws begin to queue).
+constexpr int kPieceLog2 = 17;
+
+int piece_log2(int count, int max_rank, int chunk_log2) {
+    int p = chunk_log2;
+    while (p > kPieceLog2 && claims_fit_count(count, max_rank, p - 1)) --p;
+    return p;
+}
+
 bool claims_fit(const hlf_batch_s *b, int max_rank, int chunk_log2) {
     return claims_fit_count(b->count, max_rank, chunk_log2);
 }
@@ -591,8 +617,8 @@ hlf_status launch_reduce_view(const hlf::BatchDev &d, const uint8_t *A, int max_
     hipLaunchKernelGGL(hlf::batch_queue_reset_kernel, dim3(reset_blocks), dim3(256), 0, stream,
                        queue, slots, d.count);
     if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, d, A, max_rank, p.chunk_log2, queue,
-                       slots);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, d, A, max_rank,
+                       piece_log2(d.count, max_rank, p.chunk_log2), queue, slots);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 

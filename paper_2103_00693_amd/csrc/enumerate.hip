@@ -8,12 +8,11 @@
 //                           z_i from LDS lookup tables over the nibbles of i
 //                           (method of four Russians).
 //   circuit_tile_kernel<T>  the paper's circuit, W = 1; circuit_wide_kernel W > 1.
-//   reduce_wave_kernel<WW>  W <= 3: every wavefront reduces a contiguous tile
-//                           range (stage2.h); the block combines its waves in
-//                           LDS and adds to the outputs with one atomic each.
-//   reduce_general_kernel   W > 3: element by element.
+//   reduce_kernel<W>        counts and XOR-fold in closed form, the hash on
+//                           wavefronts that take contiguous tile ranges.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "hlf_device.h"
 #include "hlf_internal.h"
@@ -113,9 +112,8 @@ __global__ __launch_bounds__(kTileThreads) void enum_wide_tile_kernel(FactorIn f
 }
 
 // ---------------------------------------------------------------------------
-// W > 1 words at an address that is not a multiple of 8, and the reduce of
-// W > 3: z_i = l ^ XOR_m Tab[m][digit m of i], 16 nibble tables of 16 entries
-// of W words (<= 32 KiB).
+// W > 1 words at an address that is not a multiple of 8: z_i = l ^ XOR_m
+// Tab[m][digit m of i], 16 nibble tables of 16 entries of W words (<= 32 KiB).
 // ---------------------------------------------------------------------------
 template <int WMAX>
 struct GenTables {
@@ -285,141 +283,78 @@ __global__ __launch_bounds__(kVecThreads) void circuit_tile_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Reduce, W <= 3: 4 waves per block, each on a contiguous range of tiles.
+// Reduce.  The first count_blocks workgroups take the counts and the XOR-fold
+// (thread j: vertex j, from column j of the basis), the others the hash, four
+// waves each on contiguous ranges of tiles and one atomic add per workgroup.
+// From W = 4 on the tile's next row comes by scalar loads under way during the
+// tile's arithmetic; below, the wave holds the rows itself.
 // ---------------------------------------------------------------------------
+constexpr int kReduceThreads = 256;
+
 template <int WW>
-__global__ __launch_bounds__(256) void reduce_wave_kernel(FactorIn f, uint64_t begin,
-                                                          uint64_t count, uint64_t tiles_per_wave,
-                                                          uint64_t *__restrict__ counts,
-                                                          uint64_t *__restrict__ hash,
-                                                          uint64_t *__restrict__ xorfold) {
-    constexpr int S = WaveReduce<WW>::S;
-    __shared__ uint64_t Bx[64 * WW];
-    __shared__ unsigned long long part_cnt[64 * WW];
-    __shared__ unsigned long long part_hash;
-    __shared__ unsigned long long part_xf[WW];
+__global__ __launch_bounds__(kReduceThreads) void reduce_kernel(FactorIn f, uint64_t begin, uint64_t count,
+                                                                uint64_t tiles_per_wave, uint32_t count_blocks,
+                                                                int accumulate, uint64_t *__restrict__ counts,
+                                                                uint64_t *__restrict__ hash,
+                                                                uint64_t *__restrict__ xorfold) {
+    constexpr int S = WaveHash<WW>::S;
+    __shared__ uint64_t part[kReduceThreads / 64];
     int r;
     if (!gate(f, begin, count, r)) return;
-    const int tid = threadIdx.x;
-    load_basis_padded<WW>(f.basis, r, Bx, tid, blockDim.x);
-    for (int j = tid; j < 64 * WW; j += blockDim.x) part_cnt[j] = 0;
-    if (tid == 0) part_hash = 0;
-    if (tid < WW) part_xf[tid] = 0;
-    uint64_t l[WW];
-#pragma unroll
-    for (int w = 0; w < WW; ++w) l[w] = f.shift[w];
-    __syncthreads();
-
-    const int lane = tid & 63;
     const uint64_t end = begin + count;
-    const uint64_t first_tile = begin >> S;
-    const uint64_t ntiles = ((end - 1) >> S) - first_tile + 1;
-    const uint64_t gw = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (tid >> 6);
-    const uint64_t t0 = gw * tiles_per_wave;
-    if (t0 < ntiles) {
-        const uint64_t t1 = (t0 + tiles_per_wave < ntiles) ? t0 + tiles_per_wave : ntiles;
-        uint64_t c0 = (first_tile + t0) << S;
-        uint64_t c1 = (first_tile + t1) << S;
-        if (c0 < begin) c0 = begin;
-        if (c1 > end) c1 = end;
-        const WavePartial<WW> p = wave_reduce_range<WW>(Bx, l, f.n, r, c0, c1);
-        if (lane == 0) {
-            if (p.hash) atomicAdd(&part_hash, (unsigned long long)p.hash);
-#pragma unroll
-            for (int w = 0; w < WW; ++w)
-                if (p.xf[w]) atomicXor(&part_xf[w], (unsigned long long)p.xf[w]);
-        }
-#pragma unroll
-        for (int w = 0; w < WW; ++w)
-            if (p.cnt[w]) atomicAdd(&part_cnt[64 * w + lane], (unsigned long long)p.cnt[w]);
-    }
-    __syncthreads();
-    for (int j = tid; j < f.n; j += blockDim.x)
-        if (part_cnt[j]) atomicAdd((unsigned long long *)&counts[j], part_cnt[j]);
-    if (tid == 0 && part_hash) atomicAdd((unsigned long long *)hash, part_hash);
-    if (xorfold && tid < WW && part_xf[tid])
-        atomicXor((unsigned long long *)&xorfold[tid], part_xf[tid]);
-}
-
-// Reduce for W > 1, element by element (tables as in enum_general_kernel).
-template <int WMAX>
-__global__ __launch_bounds__(256) void reduce_general_kernel(FactorIn f, uint64_t begin,
-                                                             uint64_t count,
-                                                             uint64_t *__restrict__ counts,
-                                                             uint64_t *__restrict__ hash,
-                                                             uint64_t *__restrict__ xorfold) {
-    using G = GenTables<WMAX>;
-    __shared__ G g;
-    __shared__ unsigned long long part[64 * WMAX];
-    int r;
-    if (!gate(f, begin, count, r)) return;
-    const int W = f.words;
-    const int n = f.n;
-    const int ndig = build_tables<WMAX>(f, r, W, false, g);
-    for (int j = threadIdx.x; j < 64 * WMAX; j += blockDim.x) part[j] = 0;
-    __syncthreads();
     const int lane = lane_id();
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    if (blockIdx.x < count_blocks) {
+        const int j = (int)blockIdx.x * kReduceThreads + (int)threadIdx.x, w = j >> 6;
+        if (w >= WW) return;  // wave-uniform
+        uint64_t col = 0;
+        for (int k = 0; k < r; ++k) col |= ((f.basis[(size_t)k * WW + w] >> lane) & 1ull) << k;
+        uint32_t odd;
+        const uint64_t c = range_count(col, (uint32_t)(f.shift[w] >> lane) & 1u, begin, end, odd);
+        const uint64_t fold = __ballot(odd);
+        if (j < f.n) counts[j] = accumulate ? counts[j] + c : c;
+        if (xorfold && lane == 0) xorfold[w] = accumulate ? xorfold[w] ^ fold : fold;
+        return;
+    }
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t ntiles = ((end - 1) >> S) - (begin >> S) + 1;
+    const uint64_t t0 = ((uint64_t)(blockIdx.x - count_blocks) * (kReduceThreads / 64) + wave) * tiles_per_wave;
     uint64_t acc = 0;
-    uint64_t xacc[WMAX];
-    uint64_t pc[WMAX];  // lane j: count of bit 64*w + j
+    if (t0 < ntiles) {
+        const uint64_t first_tile = begin >> S;
+        const uint64_t t1 = t0 + tiles_per_wave < ntiles ? t0 + tiles_per_wave : ntiles;
+        const uint64_t c0 = t0 ? (first_tile + t0) << S : begin, c1 = t1 < ntiles ? (first_tile + t1) << S : end;
+        const WaveRows<WW> b = wave_rows<WW>(f.basis, r);
+        uint64_t l[WW];
 #pragma unroll
-    for (int w = 0; w < WMAX; ++w) xacc[w] = pc[w] = 0;
-    // Every lane of a wave runs the same number of iterations (ballots).
-    const uint64_t base0 = (uint64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u);
-    for (uint64_t jb = base0; jb < count; jb += stride) {
-        const uint64_t j = jb + lane;
-        const bool valid = j < count;
-        const uint64_t i = begin + (valid ? j : 0);
-        uint64_t z[WMAX];
+        for (int w = 0; w < WW; ++w) l[w] = f.shift[w];
+        acc = wave_hash_range<WW>(b, l, c0, c1, [&](int k, uint64_t(&row)[WW]) {
 #pragma unroll
-        for (int w = 0; w < WMAX; ++w) z[w] = (w < W) ? g.l[w] : 0ull;
-        for (int m = 0; m < ndig; ++m) {
-            const int d = (int)((i >> (m * G::kDigitBits)) & (G::kEntries - 1));
-            const uint64_t *e = &g.tab[(m * G::kEntries + d) * WMAX];
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w) z[w] ^= e[w];
-        }
-        if (valid) {
-            uint64_t h = 0;
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w)
-                if (w < W) h = mix13(h ^ z[w] ^ kGamma);
-            acc += h;
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w) xacc[w] ^= z[w];
-        }
-        // Lane b counts bit 64w + b over the wave's valid solutions: bit b of
-        // z[w] across the lanes is lane b's word after the wave transpose.
-        const uint64_t vm = __ballot(valid);
-#pragma unroll
-        for (int w = 0; w < WMAX; ++w)
-            if (w < W) pc[w] += (uint64_t)__builtin_popcountll(wave_transpose64(z[w]) & vm);
+            for (int w = 0; w < WW; ++w) {
+                if constexpr (WW <= 3) row[w] = row_word<WW>(b, k, w);
+                else row[w] = f.basis[(size_t)k * WW + w];
+            }
+        });
     }
-    const uint64_t wsum = wave_sum_u64(acc);
-    if (lane == 0 && wsum) atomicAdd((unsigned long long *)hash, (unsigned long long)wsum);
-#pragma unroll
-    for (int w = 0; w < WMAX; ++w) {
-        if (w < W) {
-            const uint64_t wx = wave_xor_u64(xacc[w]);
-            if (xorfold && lane == 0 && wx) atomicXor((unsigned long long *)&xorfold[w], (unsigned long long)wx);
-            const int bit = 64 * w + lane;
-            if (bit < n && pc[w]) atomicAdd(&part[bit], (unsigned long long)pc[w]);
-        }
-    }
+    acc = wave_sum_u64(acc);
+    if (lane == 0) part[wave] = acc;
     __syncthreads();
-    for (int j = threadIdx.x; j < n; j += blockDim.x)
-        if (part[j]) atomicAdd((unsigned long long *)&counts[j], part[j]);
+    if (threadIdx.x == 0) {
+        uint64_t sum = 0;
+#pragma unroll
+        for (int v = 0; v < kReduceThreads / 64; ++v) sum += part[v];
+        if (sum) atomicAdd((unsigned long long *)hash, (unsigned long long)sum);
+    }
 }
 
-// Overwrite mode: zero the outputs first (a kernel, so the call stays
-// capturable in a graph).
+// Overwrite mode: the hash starts from zero, and for an empty range so do the
+// others (a kernel, so the call stays capturable in a graph).
 __global__ void zero_outputs_kernel(FactorIn f, uint64_t begin, uint64_t count, int n, int W,
                                     uint64_t *counts, uint64_t *hash, uint64_t *xorfold) {
     int r;
     if (!gate(f, begin, count, r)) return;
-    for (int j = threadIdx.x; j < n; j += blockDim.x) counts[j] = 0;
     if (threadIdx.x == 0) *hash = 0;
+    if (count) return;
+    for (int j = threadIdx.x; j < n; j += blockDim.x) counts[j] = 0;
     if (xorfold)
         for (int w = threadIdx.x; w < W; w += blockDim.x) xorfold[w] = 0;
 }
@@ -484,32 +419,32 @@ hlf_status launch_general(const FactorIn &f, uint64_t begin, uint64_t count, uin
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
-template <int WMAX>
-hlf_status launch_reduce_general(const FactorIn &f, uint64_t begin, uint64_t count,
-                                 uint64_t *counts, uint64_t *hash, uint64_t *xorfold,
-                                 hipStream_t stream) {
-    uint64_t blocks = (count + 255) / 256;
-    const uint64_t cap = (uint64_t)device_cu_count() * 8;
-    if (blocks > cap) blocks = cap;
-    if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL(reduce_general_kernel<WMAX>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       f, begin, count, counts, hash, xorfold);
-    return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
-}
-
 template <int WW>
-hlf_status launch_reduce_wave(const FactorIn &f, uint64_t begin, uint64_t count,
-                              uint64_t *counts, uint64_t *hash, uint64_t *xorfold,
-                              hipStream_t stream) {
-    constexpr int S = WaveReduce<WW>::S;
+hlf_status launch_reduce_t(const FactorIn &f, uint64_t begin, uint64_t count, bool accumulate, uint64_t *counts,
+                           uint64_t *hash, uint64_t *xorfold, hipStream_t stream) {
+    constexpr int S = WaveHash<WW>::S;
     const uint64_t end = begin + count;
     const uint64_t ntiles = (end < begin) ? 1 : ((end - 1) >> S) - (begin >> S) + 1;
     uint64_t waves;
-    const uint64_t tpw = tiles_per_unit_for(ntiles, (uint64_t)device_cu_count() * 32, &waves);
-    const uint64_t blocks = (waves + 3) / 4;
-    hipLaunchKernelGGL(reduce_wave_kernel<WW>, dim3((unsigned)blocks), dim3(256), 0, stream, f,
-                       begin, count, tpw, counts, hash, xorfold);
+    // Waves per CU: more than fit, so that the last ones fill in; fewer where a
+    // wave's constants are many (2^30 one-word solutions: 501 us at 16, 483 at
+    // 32, 474 at 64, 478 at 96; 2^24 of 16 words: 161 at 16 and 32, 169 at 64).
+    const uint64_t tpw = tiles_per_unit_for(ntiles, (uint64_t)device_cu_count() * (WW == 1 ? 64 : 32), &waves);
+    const uint32_t count_blocks = (uint32_t)((f.n + kReduceThreads - 1) / kReduceThreads);
+    const uint64_t blocks = count_blocks + (waves + 3) / 4;
+    hipLaunchKernelGGL(reduce_kernel<WW>, dim3((unsigned)blocks), dim3(kReduceThreads), 0, stream, f, begin, count,
+                       tpw, count_blocks, accumulate ? 1 : 0, counts, hash, xorfold);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
+}
+
+template <int... Ws>
+hlf_status launch_reduce_w(int W, const FactorIn &f, uint64_t begin, uint64_t count, bool accumulate,
+                           uint64_t *counts, uint64_t *hash, uint64_t *xorfold, hipStream_t stream,
+                           std::integer_sequence<int, Ws...>) {
+    hlf_status st = HLF_EINVAL;
+    ((W == Ws + 1 ? (st = launch_reduce_t<Ws + 1>(f, begin, count, accumulate, counts, hash, xorfold, stream), 0) : 0),
+     ...);
+    return st;
 }
 
 }  // namespace
@@ -738,12 +673,8 @@ hlf_status launch_reduce(const FactorIn &f, uint64_t begin, uint64_t count, bool
         if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
     }
     if (count == 0) return HLF_OK;
-    if (W == 1) return launch_reduce_wave<1>(f, begin, count, counts, hash, xorfold, stream);
-    if (W == 2) return launch_reduce_wave<2>(f, begin, count, counts, hash, xorfold, stream);
-    if (W == 3) return launch_reduce_wave<3>(f, begin, count, counts, hash, xorfold, stream);
-    if (W <= 4) return launch_reduce_general<4>(f, begin, count, counts, hash, xorfold, stream);
-    if (W <= 8) return launch_reduce_general<8>(f, begin, count, counts, hash, xorfold, stream);
-    return launch_reduce_general<16>(f, begin, count, counts, hash, xorfold, stream);
+    return launch_reduce_w(W, f, begin, count, accumulate, counts, hash, xorfold, stream,
+                           std::make_integer_sequence<int, HLF_MAX_WORDS>{});
 }
 
 }  // namespace hlf

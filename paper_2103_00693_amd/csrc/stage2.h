@@ -10,13 +10,6 @@
 // a per-lane constant XOR a per-tile constant.  Moving from tile T to T+1
 // changes the tile constant by F(((T+1) ^ T) << S) = B_{S-1} ^ B_{S+ctz(T+1)}
 // (the sum telescopes): the Gray-code step lifted to whole tiles.
-//
-// Over a tile that lies inside [0, 2^r) the solutions form the coset
-// z(T << S) ^ span(B_0 .. B_{S-1}).  Bit j is therefore set in exactly half of
-// them when some B_k (k < S) has bit j set, and otherwise in all or none of
-// them according to bit j of z(T << S); the XOR of the coset is zero (S >= 2).
-// The reduce routines use this for the per-qubit counts of whole tiles; the
-// hash is evaluated on every solution.
 #pragma once
 
 #include "hlf_device.h"
@@ -468,113 +461,182 @@ __device__ __forceinline__ void vec_materialise(int32_t *status, const int32_t *
 }
 
 // ---------------------------------------------------------------------------
-// Reduce on one wavefront, W = WW words (n <= 64*WW).  Tiles of 64*U indices.
+// Reduce.  Per-qubit counts and the XOR-fold of a range follow in closed form
+// (range_counts below), so only the hash visits the solutions: one wavefront
+// per contiguous range of indices, tiles of 64 U of them.  A whole tile's
+// solutions are the coset z(T << S) ^ span(B_0 .. B_{S-1}), whichever member
+// of it represents the tile, so from tile T to T + 1 the representative
+// changes by B_{S + ctz(T + 1)} alone.
+//
+// Bound by VALU issue.  The loop body is 17 instructions per solution word
+// (the first word's first step is GF(2)-linear and is applied once per lane
+// constant and once per tile): two XORs with the tile's constant in scalar
+// registers, two 64-bit products of four, two shifts, four XORs, one 64-bit
+// add; from the second word on, two three-input XORs, a shift and two XORs
+// more.  Everything per tile is scalar, which the vector unit does not wait
+// for.  A product is written so that it ends in a two-operand add, which two
+// waves can issue at once where the compiler's three-operand add takes the
+// unit for itself: 2.44 against 2.33 T hashes/s in a loop of one-word hashes
+// alone (17 instructions at the issue peak are 2.31).
 // ---------------------------------------------------------------------------
 template <int WW>
-struct WaveReduce {
-    static constexpr int U = (WW == 1) ? 16 : 8;
-    static constexpr int S = (WW == 1) ? 10 : 9;  // log2(64 * U)
+struct WaveHash {
+    // lane constants: 2 U WW registers
+    static constexpr int LOGU = WW == 1 ? 4 : WW <= 3 ? 3 : WW <= 7 ? 2 : 0;
+    static constexpr int U = 1 << LOGU;
+    static constexpr int S = 6 + LOGU;
+};
+
+__device__ __forceinline__ uint64_t mul_hash(uint64_t x, uint64_t c) {
+    const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32), cl = (uint32_t)c, ch = (uint32_t)(c >> 32);
+    const uint64_t p = (uint64_t)lo * cl + ((uint64_t)(lo * ch) << 32);
+    const uint32_t b = hi * cl, ph = (uint32_t)(p >> 32);
+    uint32_t r;
+    asm("v_add_u32_e32 %0, %1, %2" : "=v"(r) : "v"(ph), "v"(b));
+    return ((uint64_t)r << 32) | (uint32_t)p;
+}
+
+// mix13 after its first step x ^= x >> 30.
+__device__ __forceinline__ uint64_t hash_tail(uint64_t x) {
+    x = mul_hash(x, 0xBF58476D1CE4E5B9ull);
+    x ^= x >> 27;
+    x = mul_hash(x, 0x94D049BB133111EBull);
+    return x ^ (x >> 31);
+}
+
+// Lane k of a wave holds B_k, k < r (zero from r on).
+template <int WW>
+struct WaveRows {
+    uint32_t d[2 * WW];
 };
 
 template <int WW>
-struct WavePartial {
-    uint64_t hash;     // wave total (same on every lane)
-    uint64_t cnt[WW];  // this lane's count of bit 64*w + lane
-    uint64_t xf[WW];   // wave XOR (same on every lane)
-};
-
-// Counts, hash and XOR-fold over the solutions z_i, i in [c0, c1) of one
-// instance (c1 <= 2^r, r <= 62).  Bx: basis words, padded; l: shift words.
-template <int WW>
-__device__ WavePartial<WW> wave_reduce_range(const uint64_t *Bx, const uint64_t (&l)[WW], int n,
-                                             int r, uint64_t c0, uint64_t c1) {
-    constexpr int U = WaveReduce<WW>::U;
-    constexpr int S = WaveReduce<WW>::S;
+__device__ __forceinline__ WaveRows<WW> wave_rows(const uint64_t *basis, int r) {
+    WaveRows<WW> b;
     const int lane = lane_id();
-    WavePartial<WW> p;
-    p.hash = 0;
-#pragma unroll
-    for (int w = 0; w < WW; ++w) p.cnt[w] = p.xf[w] = 0;
-    if (c0 >= c1) return p;
-
-    uint64_t lo[U][WW];
-    uint64_t loh[U];  // mix13_head of word 0 (the first step of mix13 is GF(2)-linear)
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int w = 0; w < WW; ++w) lo[u][w] = l[w] ^ F_low<WW>(Bx, (uint64_t)(u * 64 + lane), S, w);
-        loh[u] = mix13_head(lo[u][0]);
-    }
-
-    uint64_t acc = 0, nfull = 0;
-    uint64_t ones[WW], pc[WW], xacc[WW];
-#pragma unroll
-    for (int w = 0; w < WW; ++w) ones[w] = pc[w] = xacc[w] = 0;
-    uint64_t Tt = c0 >> S;
-    const uint64_t Tend = ((c1 - 1) >> S) + 1;
-    uint64_t hi[WW];
-#pragma unroll
-    for (int w = 0; w < WW; ++w) hi[w] = F_tile<WW>(Bx, Tt, S, w);
-
-    for (; Tt < Tend; ++Tt) {
-        const uint64_t tb = Tt << S;
-        if (tb >= c0 && tb + (1ull << S) <= c1) {
-            // h(z) = chain over words of mix13(h ^ z_w ^ GAMMA), z = lo ^ hi
-            const uint64_t hgh = uniform64(mix13_head(hi[0] ^ kGamma));
-            uint64_t hg[WW];
-#pragma unroll
-            for (int w = 1; w < WW; ++w) hg[w] = uniform64(hi[w] ^ kGamma);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                uint64_t h = mix13_tail(loh[u] ^ hgh);
-#pragma unroll
-                for (int w = 1; w < WW; ++w) h = mix13(h ^ lo[u][w] ^ hg[w]);
-                acc += h;
-            }
-            ++nfull;
-#pragma unroll
-            for (int w = 0; w < WW; ++w) ones[w] += ((l[w] ^ hi[w]) >> lane) & 1ull;
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint64_t i = tb + (uint64_t)(u * 64 + lane);
-                const bool valid = (i >= c0) && (i < c1);
-                uint64_t z[WW];
-#pragma unroll
-                for (int w = 0; w < WW; ++w) z[w] = lo[u][w] ^ hi[w];
-                if (valid) {
-                    uint64_t h = 0;
-#pragma unroll
-                    for (int w = 0; w < WW; ++w) {
-                        h = mix13(h ^ z[w] ^ kGamma);
-                        xacc[w] ^= z[w];
-                    }
-                    acc += h;
-                }
-                // Lane b counts bit 64w + b over the valid lanes: bit b of z[w]
-                // across the lanes is lane b's word after the wave transpose
-                // (bits at or past n are zero in every solution).
-                const uint64_t vm = __ballot(valid);
-#pragma unroll
-                for (int w = 0; w < WW; ++w)
-                    pc[w] += (uint64_t)__builtin_popcountll(wave_transpose64(z[w]) & vm);
-            }
-        }
-#pragma unroll
-        for (int w = 0; w < WW; ++w) hi[w] ^= tile_step<WW>(Bx, Tt, S, w);
-    }
-
-    p.hash = wave_sum_u64(acc);
 #pragma unroll
     for (int w = 0; w < WW; ++w) {
-        p.xf[w] = wave_xor_u64(xacc[w]);
-        uint64_t orS = 0;
-        for (int k = 0; k < S && k < r; ++k) orS |= Bx[k * WW + w];
-        uint64_t c = pc[w];
-        if (nfull) c += ((orS >> lane) & 1ull) ? (nfull << (S - 1)) : (ones[w] << S);
-        p.cnt[w] = c;
+        const uint64_t v = lane < r ? basis[(size_t)lane * WW + w] : 0ull;
+        b.d[2 * w] = (uint32_t)v;
+        b.d[2 * w + 1] = (uint32_t)(v >> 32);
     }
-    return p;
+    return b;
+}
+
+template <int WW>
+__device__ __forceinline__ uint64_t row_word(const WaveRows<WW> &b, int k, int w) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)b.d[2 * w], k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)b.d[2 * w + 1], k);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// This lane's share of the sum of h(z_i), i in [c0, c1) (c0 < c1 <= 2^r, both
+// wave-uniform).  l: the shift, wave-uniform.  next_row(k, row): word w of
+// B_k to row[w], k wave-uniform.
+template <int WW, typename NextRow>
+__device__ __forceinline__ uint64_t wave_hash_range(const WaveRows<WW> &b, const uint64_t (&l)[WW], uint64_t c0,
+                                                    uint64_t c1, NextRow next_row) {
+    constexpr int U = WaveHash<WW>::U, LOGU = WaveHash<WW>::LOGU, S = WaveHash<WW>::S;
+    constexpr uint64_t M = (1ull << S) - 1;
+    const uint32_t lane = (uint32_t)lane_id();
+    // Lane constants F(64 u + lane): the lane's part, and for u the rows at
+    // the bits of c(64 u) = g(u) << 6, with bit 5 for odd u.
+    uint64_t lo[U][WW];
+    const uint32_t cx = lane ^ (lane >> 1);
+#pragma unroll
+    for (int w = 0; w < WW; ++w) {
+        uint32_t v0 = 0, v1 = 0;
+        uint64_t row5 = 0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const uint64_t e = row_word<WW>(b, j, w);
+            const uint32_t m = (uint32_t)((int)(cx << (31 - j)) >> 31);
+            v0 ^= m & (uint32_t)e;
+            v1 ^= m & (uint32_t)(e >> 32);
+            row5 = e;
+        }
+        uint64_t rows[LOGU + 1];
+#pragma unroll
+        for (int j = 0; j < LOGU; ++j) rows[j] = row_word<WW>(b, 6 + j, w);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint64_t f = (u & 1) ? row5 : 0ull;
+#pragma unroll
+            for (int j = 0; j < LOGU; ++j)
+                if (((u ^ (u >> 1)) >> j) & 1) f ^= rows[j];
+            lo[u][w] = (((uint64_t)v1 << 32) | v0) ^ f;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) lo[u][0] = mix13_head(lo[u][0]);
+
+    uint64_t T = c0 >> S;
+    const uint64_t Tend = ((c1 - 1) >> S) + 1;
+    const uint64_t full0 = (c0 + M) >> S, full1 = c1 >> S;
+    // Tile constant l ^ gamma ^ F(T << S) without its bit S - 1.
+    uint64_t hi[WW];
+    const bool on = __builtin_amdgcn_inverse_ballot_w64((T ^ (T >> 1)) << S);
+#pragma unroll
+    for (int w = 0; w < WW; ++w) {
+        uint32_t h[2] = {on ? b.d[2 * w] : 0u, on ? b.d[2 * w + 1] : 0u};
+        wave_xor_dwords<2>(h);
+        hi[w] = l[w] ^ kGamma ^ (((uint64_t)h[1] << 32) | h[0]);
+    }
+    uint64_t acc = 0;
+    for (;;) {
+        const bool more = T + 1 < Tend;
+        uint64_t row[WW];
+        if (more) next_row(S + __builtin_ctzll(T + 1), row);
+        const uint64_t h0 = mix13_head(hi[0]);
+        auto hash_of = [&](int u) {
+            uint64_t h = hash_tail(lo[u][0] ^ h0);
+#pragma unroll
+            for (int w = 1; w < WW; ++w) h = hash_tail(mix13_head(h ^ lo[u][w] ^ hi[w]));
+            return h;
+        };
+        if (U > 1 && T >= full0 && T < full1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc += hash_of(u);
+        } else {
+            // The first or last tile of the range, by its indices: the
+            // representative leaves out bit S - 1 of g(T << S), which for odd
+            // T puts index M - x of the tile in the place of x.  (With many
+            // words the comparisons cost less than a second copy of the body.)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t x = (uint64_t)(64 * u) + lane, i = (T << S) + ((T & 1ull) ? M - x : x);
+                const uint64_t h = hash_of(u);
+                acc += (i >= c0 && i < c1) ? h : 0ull;
+            }
+        }
+        if (!more) break;
+#pragma unroll
+        for (int w = 0; w < WW; ++w) hi[w] ^= row[w];
+        ++T;
+    }
+    return acc;
+}
+
+// Bit j of every solution of [begin, end) (begin < end <= 2^r): how many have
+// it set, and the parity of that for the XOR-fold.  col: bit k is B_k[j]; lj =
+// l[j].  The range is cut into aligned blocks of 2^K indices, each a coset
+// z(a) ^ span(B_0 .. B_{K-1}): the bit is set in half of it if some B_k, k < K,
+// has it, else in all or none as in z(a).
+__device__ __forceinline__ uint64_t range_count(uint64_t col, uint32_t lj, uint64_t begin, uint64_t end,
+                                                uint32_t &odd) {
+    uint64_t count = 0;
+    odd = 0;
+    for (uint64_t a = begin; a < end;) {
+        const int up = a ? __builtin_ctzll(a) : 63, fit = 63 - __builtin_clzll(end - a);
+        const int K = up < fit ? up : fit;
+        const uint64_t size = 1ull << K;
+        const uint32_t z = lj ^ ((uint32_t)__builtin_popcountll(col & (a ^ (a >> 1))) & 1u);
+        const uint64_t c = (col & (size - 1)) ? size >> 1 : z ? size : 0ull;
+        count += c;
+        odd ^= (uint32_t)c & 1u;
+        a += size;
+    }
+    return count;
 }
 
 }  // namespace hlf
