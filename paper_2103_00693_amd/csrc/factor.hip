@@ -8,10 +8,10 @@
 //     its rows in VGPRs, pivots are found with a ballot and the pivot row is
 //     broadcast with readlane -- no barriers in the elimination;
 //   * factor_workgroup_kernel: one workgroup per instance for n <= 1024, one
-//     row per thread in VGPRs, Gauss-Jordan in blocks of 8 columns: the
-//     pivot search runs on bit-planes of the rows' 8-bit slices in one wave,
-//     then every row applies its block update with two lookups per word in
-//     tables of XOR combinations of the block's pivot rows (LDS).
+//     row per thread in VGPRs, Gauss-Jordan in panels of 64 columns: one wave
+//     finds a panel's pivots on one word per row, then every row applies the
+//     panel with 16 lookups per word in tables of XOR combinations of the
+//     panel's pivot rows (LDS).
 // Both variants produce the canonical record defined in hlf.h (the RREF is
 // unique, so the pivot rows chosen do not matter).
 #include "factor_wave.h"
@@ -275,81 +275,268 @@ __global__ __launch_bounds__(64) void factor_wave_kernel(const uint64_t *__restr
 
 // ---------------------------------------------------------------------------
 // A1-A4, workgroup variant: n <= 64*WMAX <= 1024, 64*W threads, thread i
-// holds row i.  The LDS matrix `mat` (n rows of W words) first holds A for
-// the symmetry check, then the RREF rows (0..r-1) and the kernel vectors
-// (r..n-1).
+// holds row i.  Gauss-Jordan in panels of 64 columns, one word of every row:
+//
+//   1. rows that are no pivot yet and not zero in the panel are listed in LDS;
+//   2. one wave finds the panel's pivots from the list (panel_pivots below),
+//      on panel words alone, 64 rows at a time, one per lane.  Elimination is
+//      in place: where a pivot has been added to a row, the row's bit at the
+//      pivot's column stays set, so that a row's bits at pivot columns come to
+//      say which start-of-panel pivot rows it is the sum of (tau), and those
+//      at the other columns are its entries there;
+//   3. every row's tag t is the XOR of the tau of the pivots of the columns
+//      that it has set (13 table lookups, five bits each), and its own tau if
+//      it has become a pivot: t says which start-of-panel pivot rows to add;
+//   4. the pivot rows lie in LDS; every word from the panel's on gets 13 tables
+//      of 32 XOR combinations, and every row adds one entry of each to it.
+//      (Words left of the panel are zero in rows that are no pivot yet.)
+//
+// The next panel's word is brought up to date first, so that its pivots are
+// found by one wave while the others work on the words behind it.
+//
+// Which rows become pivots does not matter: the pivot columns are the leading
+// ones of the row space, and the reduced echelon form is unique.
+//
+// Bound by the chain of one pivot after the other: a column costs some 17
+// instructions of one wave, which issues one in five cycles at best.  Tables
+// of 32 entries of 8 bytes spread over all 64 LDS banks: 530 cycles per word
+// for 1024 rows, against 1080 with tables of 16, which use half of them.
+// Measured at n = 1024 (32x32 grid, half the bonds), stage 1 with the packing:
+// 164 us a pass, against 528 with panels of 8 columns, whose pivots all
+// waves searched together with two barriers a column.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int lower_bound_int(const int *a, int len, int key) {
-    int lo = 0, hi = len;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < key) lo = mid + 1; else hi = mid;
+constexpr int kTabGroups = 13;                    // groups of five bits of a word
+constexpr int kTabWords = kTabGroups * 32;
+
+template <int WMAX>
+struct PanelShared {
+    static constexpr int NP = 64 * WMAX;
+    static constexpr int kStride = NP + 1;  // words of a column of `mat`, odd against bank conflicts
+    // mat holds, in turn: A word-major (word w of row i at w*kStride + i); the
+    // panel step's arrays; the reduced rows by pivot column, transposed in
+    // place into the kernel vectors by free column.
+    struct Panel {
+        uint64_t tab[WMAX * kTabWords];   // [word][group][32]
+        uint64_t start[WMAX * 64];        // [word][column]: start-of-panel pivot rows
+        uint64_t ttab[kTabWords];         // the tables of tau
+        uint64_t tau[64];                 // by column
+        uint64_t base[64];                // the basis found so far (panel_pivots)
+        uint64_t btab[kTabWords];         // its tables
+        uint64_t cand_x[NP];
+        uint16_t cand_row[NP];
+    };
+    union alignas(16) {
+        uint64_t mat[WMAX * kStride];
+        Panel pan;
+    };
+    uint64_t pivots[WMAX];     // pivot columns, by panel
+    uint64_t diag[WMAX];
+    int qacc[NP];
+    uint16_t pivcol[NP];       // row -> its pivot column, 0xFFFF if none
+    uint16_t pivlist[NP];
+    int ncand[2];
+    int bad, internal;
+};
+
+__device__ __forceinline__ uint32_t lane_select(uint64_t mask, uint32_t v, uint32_t other) {
+    return __builtin_amdgcn_inverse_ballot_w64(mask) ? v : other;
+}
+
+// x ^ (m & p), one instruction.
+__device__ __forceinline__ uint32_t xor_masked(uint32_t x, uint32_t m, uint32_t p) {
+    return __builtin_amdgcn_bitop3_b32(x, m, p, 0x78);
+}
+
+// The 13 tables of the XOR combinations of vec[0..63], by one wave: lane
+// 4g + q fills entries 8q .. 8q + 7 of group g (the last group has four
+// vectors).
+__device__ __forceinline__ void fill_tables(const uint64_t *vec, uint64_t *tab) {
+    const int lane = lane_id(), g = lane >> 2, q = lane & 3;
+    if (g >= kTabGroups) return;
+    const uint64_t *v = vec + 5 * g;
+    const uint64_t s0 = v[0], s1 = v[1], s2 = v[2], s3 = v[3], s4 = g < 12 ? v[4] : 0ull;
+    uint64_t e[8];
+    e[0] = ((q & 1) ? s3 : 0ull) ^ ((q & 2) ? s4 : 0ull);
+    e[1] = e[0] ^ s0;
+    e[2] = e[0] ^ s1;
+    e[3] = e[1] ^ s1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) e[4 + k] = e[k] ^ s2;
+    uint64_t *t = tab + 8 * lane;  // 32 g + 8 q
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = e[k];
+}
+
+// Places of the entries of v in a word's tables.
+__device__ __forceinline__ void table_places(uint64_t v, uint32_t (&at)[kTabGroups]) {
+#pragma unroll
+    for (int g = 0; g < kTabGroups; ++g) at[g] = 32 * g + ((uint32_t)(v >> (5 * g)) & 31u);
+}
+
+// (The scheduling barrier keeps the reads together: left alone the compiler
+// waits for each before the next, 750 cycles per word for one wave.)
+__device__ __forceinline__ uint64_t table_sum(const uint64_t *tab, const uint32_t (&at)[kTabGroups]) {
+    uint64_t e[kTabGroups];
+#pragma unroll
+    for (int g = 0; g < kTabGroups; ++g) e[g] = tab[at[g]];
+    __builtin_amdgcn_sched_barrier(0);
+    uint64_t v = e[0];
+#pragma unroll
+    for (int g = 1; g < kTabGroups; ++g) v ^= e[g];
+    return v;
+}
+
+// 32 columns of the first 64 listed rows, one row per lane (panel word xh:xl):
+// the lowest open row that has the column becomes its pivot, stays in its lane
+// and is reduced with the others.
+template <bool kHalf>
+__device__ __forceinline__ void pivot_columns(uint32_t &xl, uint32_t &xh, uint32_t &col, uint64_t &open,
+                                              uint32_t &need) {
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+        const uint64_t has = __ballot((kHalf ? xh : xl) & (1u << c));
+        const uint64_t cand = has & open;
+        if (cand != 0) {  // wave-uniform
+            const int L = __builtin_ctzll(cand);
+            const uint64_t me = 1ull << L;
+            uint32_t m = lane_select(has & ~me, ~0u, 0u);
+            asm("" : "+v"(m));  // keep the mask: one instruction per word below
+            uint32_t ph = (uint32_t)__builtin_amdgcn_readlane((int)xh, L);
+            uint32_t pl = (uint32_t)__builtin_amdgcn_readlane((int)xl, L);
+            if (kHalf) ph &= ~(1u << c);
+            else pl &= ~(1u << c);
+            xh = xor_masked(xh, m, ph);
+            xl = xor_masked(xl, m, pl);
+            col = lane_select(me, (uint32_t)((kHalf ? 32 : 0) + c), col);
+            open &= ~me;
+            need &= ~(1u << c);
+        }
     }
-    return lo;
+}
+
+// Step 2, by one wave: the pivots of a panel of kb columns from nc listed
+// rows.  Writes tau by column, the rows' pivot columns and returns the pivot
+// mask (wave-uniform).
+template <int WMAX>
+__device__ uint64_t panel_pivots(PanelShared<WMAX> &sm, int nc, int kb, int panel) {
+    auto &P = sm.pan;
+    const int lane = lane_id();
+    const uint64_t all = kb < 64 ? (1ull << kb) - 1 : ~0ull;
+    uint32_t xl = 0, xh = 0, row = 0, col = ~0u;
+    if (lane < nc) {
+        xl = (uint32_t)P.cand_x[lane];
+        xh = (uint32_t)(P.cand_x[lane] >> 32);
+        row = P.cand_row[lane];
+    }
+    uint64_t open = __ballot((xl | xh) != 0u);
+    uint32_t need_l = (uint32_t)all, need_h = (uint32_t)(all >> 32);  // columns without a pivot yet
+    pivot_columns<false>(xl, xh, col, open, need_l);
+    pivot_columns<true>(xl, xh, col, open, need_h);
+    uint64_t need = ((uint64_t)need_h << 32) | need_l;
+    // Further rows, 64 at a time: the basis found so far is added where they
+    // have its columns, what is left has entries in columns of `need` only.  A
+    // new pivot moves to a lane that holds none.
+    for (int first = 64; first < nc && need; first += 64) {
+        P.base[lane] = 0;
+        wave_lds_sync();
+        if (col < 64u) P.base[col] = ((uint64_t)xh << 32) | xl;
+        wave_lds_sync();
+        fill_tables(P.base, P.btab);
+        wave_lds_sync();
+        uint64_t y = 0;
+        uint32_t yrow = 0;
+        if (first + lane < nc) {
+            const uint64_t v = P.cand_x[first + lane];
+            yrow = P.cand_row[first + lane];
+            uint32_t at[kTabGroups];
+            table_places(v, at);
+            y = (v & need) ^ table_sum(P.btab, at);
+        }
+        uint64_t left = __ballot((y & need) != 0ull);
+        for (uint64_t cols = need; cols && left; cols &= cols - 1) {
+            const int c = __builtin_ctzll(cols);
+            const uint64_t has = __ballot((y >> c) & 1ull) & left;
+            if (has == 0) continue;
+            const int L = __builtin_ctzll(has);
+            const uint64_t bit = 1ull << c, px = readlane64(y, L), add = px & ~bit;
+            const uint32_t prow = (uint32_t)__builtin_amdgcn_readlane((int)yrow, L);
+            left &= ~(1ull << L);
+            if ((y & bit) && lane != L) y ^= add;
+            const uint32_t ma = (((c < 32 ? xl : xh) >> (c & 31)) & 1u) ? ~0u : 0u;
+            const uint64_t held = __ballot(col < 64u);
+            const uint64_t me = ~held & (held + 1);  // the lowest lane without a pivot
+            xl = lane_select(me, (uint32_t)px, xl ^ (ma & (uint32_t)add));
+            xh = lane_select(me, (uint32_t)(px >> 32), xh ^ (ma & (uint32_t)(add >> 32)));
+            col = lane_select(me, (uint32_t)c, col);
+            row = lane_select(me, prow, row);
+            need &= ~bit;
+            left &= __ballot((y & need) != 0ull);
+        }
+    }
+    const uint64_t found = all & ~need;
+    P.tau[lane] = 0;
+    wave_lds_sync();
+    if (col < 64u) {
+        P.tau[col] = (((uint64_t)xh << 32) | xl) & found;
+        sm.pivcol[row] = (uint16_t)(64 * panel + (int)col);
+    }
+    return found;
 }
 
 template <int WMAX>
-__global__ __launch_bounds__(1024) void factor_workgroup_kernel(const uint64_t *__restrict__ rows,
-                                                                int n, int W, FactorOut out,
-                                                                int keep_bad) {
+__global__ __launch_bounds__(64 * WMAX) void factor_workgroup_kernel(const uint64_t *__restrict__ rows,
+                                                                     int n, int W, FactorOut out,
+                                                                     int keep_bad) {
     if (keep_bad && *(volatile int32_t *)out.status != HLF_OK) return;
-    constexpr int NP = 64 * WMAX;
-    constexpr int kMatWords = 64 * WMAX * WMAX > 256 * WMAX ? 64 * WMAX * WMAX : 256 * WMAX;
-    __shared__ uint64_t mat[kMatWords];
-    __shared__ uint64_t prow[8 * WMAX];
-    __shared__ int piv[64 * WMAX];
-    __shared__ int freec[64 * WMAX];
-    __shared__ int qacc[64 * WMAX];
-    __shared__ __align__(16) uint8_t sl8[1024];
-    __shared__ uint16_t pivmark[64 * WMAX];  // block * 8 + j for the block's j-th pivot row
-    __shared__ uint32_t ttab[32];            // tag of a slice: ttab[low nibble] ^ ttab[16 + high]
-    __shared__ __align__(16) uint32_t blkstate[16];
-    __shared__ int blk[2];
-    __shared__ uint32_t wmask;
-    __shared__ unsigned long long shiftw[WMAX];
-    __shared__ int flag_bad, flag_internal;
-
+    using Sm = PanelShared<WMAX>;
+    constexpr int ST = Sm::kStride;
+    __shared__ Sm sm;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int nthr = blockDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nthr = 64 * W;
 
-    // `mat` holds, in turn: A word-major (word w of row i at w*NP + i) for the
-    // symmetry check; the block tables of the elimination; the RREF rows and
-    // the kernel vectors, row-major.
-    uint64_t row[WMAX];
+    // A into LDS with consecutive loads: this thread's elements tid + k*nthr
+    // are word w0 of rows i0 + 64k.
+    const int i0 = tid / W, w0 = tid - i0 * W;
+    {
+        uint64_t v[WMAX];
 #pragma unroll
-    for (int w = 0; w < WMAX; ++w) {
-        row[w] = (tid < n && w < W) ? rows[tid * W + w] : 0ull;
-        mat[w * NP + tid] = row[w];
+        for (int k = 0; k < WMAX; ++k) v[k] = (k < W && i0 + 64 * k < n) ? rows[tid + k * nthr] : 0ull;
+#pragma unroll
+        for (int k = 0; k < WMAX; ++k)
+            if (k < W) sm.mat[w0 * ST + i0 + 64 * k] = v[k];
     }
-    if (tid < WMAX) shiftw[tid] = 0;
-    pivmark[tid] = 0xFFFFu;
+    sm.pivcol[tid] = 0xFFFFu;
+    sm.qacc[tid] = 0;
     if (tid == 0) {
-        flag_bad = 0;
-        flag_internal = 0;
+        sm.bad = 0;
+        sm.internal = 0;
+        sm.ncand[0] = sm.ncand[1] = 0;
     }
     __syncthreads();
+    uint64_t row[WMAX];
+#pragma unroll
+    for (int w = 0; w < WMAX; ++w) row[w] = w < W ? sm.mat[w * ST + tid] : 0ull;
 
+    // Pad bits, and the symmetry of the tile pairs.
     bool bad = false;
     const uint64_t lm = last_word_mask(n);
 #pragma unroll
-    for (int w = 0; w < WMAX; ++w)
+    for (int w = 0; w < WMAX; ++w) {
         if (w == W - 1 && (row[w] & ~lm)) bad = true;
-    // Symmetry: tile pairs (I, J), I <= J < W, spread over the waves.
-    {
-        const int nwaves = nthr >> 6;
-        int pidx = 0;
-        for (int I = 0; I < W; ++I)
-            for (int J = I; J < W; ++J, ++pidx) {
-                if (pidx % nwaves != wave) continue;
-                if (tile_pair_asym(mat[J * NP + 64 * I + lane], mat[I * NP + 64 * J + lane]))
-                    bad = true;
-            }
+        if (w == wave) {
+            const uint64_t d = __ballot((row[w] >> lane) & 1ull);
+            if (lane == 0) sm.diag[wave] = d;
+        }
     }
-    if (bad) flag_bad = 1;
+    for (int d = 0; 2 * d <= W; ++d) {  // tile pairs (I, I + d mod W), wave I
+        const int J = wave + d < W ? wave + d : wave + d - W;
+        if (tile_pair_asym(sm.mat[J * ST + 64 * wave + lane], sm.mat[wave * ST + 64 * J + lane])) bad = true;
+    }
+    if (bad) sm.bad = 1;
     __syncthreads();
-    if (flag_bad) {
+    if (sm.bad) {
         if (tid == 0) {
             *out.status = HLF_ENOTSYM;
             *out.rank = 0;
@@ -357,260 +544,197 @@ __global__ __launch_bounds__(1024) void factor_workgroup_kernel(const uint64_t *
         return;
     }
 
-    // Gauss-Jordan in blocks of 8 columns (the blocking of Arlazarov,
-    // Dinic, Kronrod and Faradzev, the "Four Russians").  Within a block only
-    // the 8-bit slice s of every row takes part in the elimination: the
-    // pivot of column c is the lowest-index row that is not yet a pivot and
-    // has bit c of its current slice set, and every row keeps a tag tau (bit
-    // j set: the block's j-th pivot row, as it stood when the block began,
-    // has been added to it).  One column step maps the state (slice, tag) of
-    // every row other than that column's pivot by a linear map over GF(2)
-    // (add the pivot's state, plus bit j to the tag, if bit c is set), so
-    // the state of such a row is a linear function of its starting slice:
-    // the XOR of the states reached from the 8 unit slices.  Wave 0 holds the
-    // current slices of all rows as 8 bit-planes, 16 rows per lane, so the
-    // candidates of column c are one plane ANDed with the not-yet-pivot mask
-    // and the pivot is its lowest set bit (a ballot and a readlane); the rows
-    // with bit c then take the pivot's current slice, one XOR per later
-    // plane.  For the tags, lanes 0-7 track the states of the 8 unit slices
-    // and lanes 8-15 the pivots' own states; a pivot's state is the XOR of
-    // the unit states over its starting slice (a DPP reduction).  The block
-    // ends with every row's tag; the current value of every row is then its
-    // start-of-block value plus the XOR of the pivot rows in its tag, so two
-    // lookups per word in 16-entry tables (one per half of the tag) update
-    // every row, pivot rows included.
-    int r = 0, nfree = 0;
+    auto &P = sm.pan;
     bool used = false;
-    int myk = -1;
-    uint32_t unused16 = 0;  // wave 0: bit b of lane l <=> row 16l+b is not a pivot
-    if (wave == 0)
-        for (int b = 0; b < 16; ++b)
-            if (16 * lane + b < n) unused16 |= 1u << b;
-    uint64_t cur = row[0];  // word c0 / 64 of this row, kept current
-    for (int c0 = 0; c0 < n; c0 += 8) {
-        const int kb = (n - c0) < 8 ? (n - c0) : 8;
-        const int cw = c0 >> 6;
-        const int blkno = c0 >> 3;
-        if (cw && (c0 & 63) == 0) {
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w)
-                if (w == cw) cur = row[w];
+    uint64_t x = row[0];  // the panel's word, up to date
+    uint64_t t = 0;       // the last panel's tag; its words from p + 1 on are due
+    for (int p = 0;; ++p) {
+        // 1. the list of panel p
+        const bool open = !used && x != 0ull;
+        const uint64_t opens = __ballot(open);
+        if (opens) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&sm.ncand[p & 1], __builtin_popcountll(opens));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (open) {
+                at += __builtin_popcountll(opens & ((1ull << lane) - 1ull));
+                P.cand_x[at] = x;
+                P.cand_row[at] = (uint16_t)tid;
+            }
         }
-        const uint32_t sl = (uint32_t)(cur >> (c0 & 63)) & 0xFFu;
-        sl8[tid] = (uint8_t)sl;
         __syncthreads();
-
+        // 2. its pivots, beside the last panel's words behind it
         if (wave == 0) {
-            // cp[u]: bit b of lane l <=> bit u of the current slice of row
-            // 16l+b: the 16 slices of the lane, as two 8x8 bit matrices (byte
-            // = row, bit = column), transposed with three delta swaps.  Lanes
-            // past the last row hold stale bytes; their rows are never
-            // candidates (unused16 is 0 there).
-            const u32x4 sq = *reinterpret_cast<const u32x4 *>(&sl8[16 * lane]);
-            auto transpose8 = [](uint64_t x) {
-                uint64_t t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
-                x ^= t ^ (t << 7);
-                t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
-                x ^= t ^ (t << 14);
-                t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
-                x ^= t ^ (t << 28);
-                return x;
-            };
-            const uint64_t p0 = transpose8(((uint64_t)sq.y << 32) | sq.x);
-            const uint64_t p1 = transpose8(((uint64_t)sq.w << 32) | sq.z);
-            uint32_t cp[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                cp[k] = (uint32_t)((p0 >> (8 * k)) & 0xFFu) | ((uint32_t)((p1 >> (8 * k)) & 0xFFu) << 8);
-            // Lane k < 8: state of unit slice e_k (slice | tag << 8); lane 8+j:
-            // state of pivot j after its own step.
-            uint32_t st = (lane < 8) ? (1u << lane) : 0u;
-            int m = 0;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                if (t >= kb) break;
-                const uint32_t cm = cp[t] & unused16;
-                const uint64_t bm = __ballot(cm != 0u);
-                if (bm == 0) {
-                    if (lane == 0) freec[nfree] = c0 + t;
-                    ++nfree;
-                    continue;
-                }
-                const int L = __builtin_ctzll(bm);
-                const int b = __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)cm, L));
-                const uint32_t rbit = (lane == L) ? (1u << b) : 0u;
-                // Rows with bit t set, the pivot excluded, add the pivot's
-                // current slice; its bit t+1 is read directly so the next
-                // column's candidates do not wait for the unit states.
-                const uint32_t cpx = cp[t] & ~rbit;
-                unused16 &= ~rbit;
-                if (t + 1 < 8) {
-                    const uint32_t c1 =
-                        ((uint32_t)__builtin_amdgcn_readlane((int)cp[t + 1 < 8 ? t + 1 : 7], L) >> b) & 1u;
-                    if (c1) cp[t + 1 < 8 ? t + 1 : 7] ^= cpx;
-                }
-                const int q = b >> 2;
-                const uint32_t sw = q == 0 ? sq.x : q == 1 ? sq.y : q == 2 ? sq.z : sq.w;
-                const uint32_t sp =
-                    ((uint32_t)__builtin_amdgcn_readlane((int)sw, L) >> (8 * (b & 3))) & 0xFFu;
-                const uint32_t xr =
-                    xor_lanes0to7((lane < 8 && ((sp >> lane) & 1u)) ? st : 0u);
-#pragma unroll
-                for (int u = t + 2; u < 8; ++u)
-                    if ((xr >> u) & 1u) cp[u] ^= cpx;
-                const uint32_t upd = xr ^ (1u << (8 + m));
-                if (lane < 8 + m && ((st >> t) & 1u)) st ^= upd;
-                if (lane == 8 + m) st = xr;
-                if (lane == 0) {
-                    piv[r + m] = c0 + t;
-                    pivmark[16 * L + b] = (uint16_t)(8 * blkno + m);
-                }
-                ++m;
-            }
-            // Tag of a row = XOR of the unit tags over its starting slice,
-            // as two 16-entry tables (low and high nibble): lane l < 32 fills
-            // entry l & 15 of table l >> 4.
-            uint32_t us[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) us[k] = ((uint32_t)__builtin_amdgcn_readlane((int)st, k) >> 8) & 0xFFu;
-            if (lane < 32) {
-                const int hi = lane >> 4, e = lane & 15;
-                uint32_t v = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if ((e >> k) & 1) v ^= hi ? us[4 + k] : us[k];
-                ttab[lane] = v;
-            }
-            if (lane >= 8 && lane < 16) blkstate[lane] = (st >> 8) & 0xFFu;
+            __builtin_amdgcn_s_setprio(3);
+            const int kb = n - 64 * p < 64 ? n - 64 * p : 64;
+            const uint64_t found = panel_pivots<WMAX>(sm, __builtin_amdgcn_readfirstlane(sm.ncand[p & 1]), kb, p);
             if (lane == 0) {
-                blk[0] = m;
-                blk[1] = nfree;
+                sm.pivots[p] = found;
+                sm.ncand[(p + 1) & 1] = 0;
             }
+            __builtin_amdgcn_s_setprio(0);
         }
-        __syncthreads();
-        const int m = blk[0];
-        nfree = blk[1];
-        uint32_t tau = 0;
-        if (m > 0 && tid < n) {
-            tau = ttab[sl & 15u] ^ ttab[16 + (sl >> 4)];
-            const uint32_t mk = pivmark[tid];
-            if ((int)(mk >> 3) == blkno) {
-                const int j = (int)(mk & 7u);
-                used = true;
-                myk = r + j;
-                tau = blkstate[8 + j];
-#pragma unroll
-                for (int w = 0; w < WMAX; ++w) prow[j * WMAX + w] = row[w];
-            }
-        }
-        if (tid == 0) wmask = 0;
-        r += m;
-        if (m == 0) continue;
-        __syncthreads();
-        // Two tables per word w of the block's pivot rows (as they stood when
-        // the block began): L[e] = XOR of pivot rows j < 4 with bit j of e
-        // set at mat[w*32 + e], H[e] the same for pivot rows 4 + j at
-        // mat[w*32 + 16 + e]; word w of a row's update is L[tau & 15] ^
-        // H[tau >> 4].  Thread (w, e) = (tid / 32, tid % 32) fills one entry.
-        // Words that are zero in every pivot row (all words left of the
-        // block's word, since a row that is not yet a pivot is zero in every
-        // column already eliminated or found free) are skipped in the lookup;
-        // wmask records the others, one ballot per wave for its two words.
-        {
-            const int w = tid >> 5, e = tid & 31;
-            const int half = e >> 4, idx = e & 15;
-            uint64_t v = 0;
-            if (w < W) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (4 * half + k < m && ((idx >> k) & 1)) v ^= prow[(4 * half + k) * WMAX + w];
-                mat[w * 32 + e] = v;
-            }
-            const uint64_t nzb = __ballot(v != 0ull);
-            if (lane == 0 && nzb)
-                atomicOr(&wmask, ((uint32_t)nzb ? 1u << (2 * wave) : 0u) |
-                                     ((uint32_t)(nzb >> 32) ? 1u << (2 * wave + 1) : 0u));
-        }
-        __syncthreads();
-        const uint32_t wm = (uint32_t)__builtin_amdgcn_readfirstlane((int)wmask);
-        if (tau) {
-            const uint32_t tl = tau & 15u, th = 16u + (tau >> 4);
-            uint64_t tv[WMAX];
+        if (__ballot(t != 0ull)) {
+            uint32_t at[kTabGroups];
+            table_places(t, at);
 #pragma unroll
             for (int w = 0; w < WMAX; ++w)
-                tv[w] = ((wm >> w) & 1u) ? (mat[w * 32 + tl] ^ mat[w * 32 + th]) : 0ull;
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w) row[w] ^= tv[w];
-            if ((wm >> cw) & 1u) cur ^= mat[cw * 32 + tl] ^ mat[cw * 32 + th];
+                if (w > p && w < W) row[w] ^= table_sum(P.tab + w * kTabWords, at);
         }
-        // The next block's first write to sl8, the block state or the table
-        // comes after at least one more barrier.
-    }
-    __syncthreads();
-    if (used)
-#pragma unroll
-        for (int w = 0; w < WMAX; ++w)
-            if (w < W) mat[myk * W + w] = row[w];
-    const int nk = n - r;
-    if (tid < nk) qacc[tid] = 0;
-    __syncthreads();
-
-    // Kernel vectors: word w of k_f collects RREF[k][f] at the pivots of word w.
-    for (int idx = tid; idx < nk * W; idx += nthr) {
-        const int j = idx / W, w = idx - j * W;
-        const int f = freec[j];
-        uint64_t v = ((f >> 6) == w) ? (1ull << (f & 63)) : 0ull;
-        const int klo = lower_bound_int(piv, r, 64 * w);
-        const int khi = lower_bound_int(piv, r, 64 * w + 64);
-        for (int k = klo; k < khi; ++k)
-            if ((mat[k * W + (f >> 6)] >> (f & 63)) & 1ull) v |= 1ull << (piv[k] & 63);
-        mat[(r + j) * W + w] = v;
-        if (out.kernel) out.kernel[j * W + w] = v;
-    }
-    __syncthreads();
-
-    // q(k_f): thread i adds popcount(A_i & k_f) when bit i of k_f is set.
-    if (tid < n) {
-        uint64_t arow[WMAX];
-#pragma unroll
-        for (int w = 0; w < WMAX; ++w) arow[w] = (w < W) ? rows[tid * W + w] : 0ull;
-        for (int j = 0; j < nk; ++j) {
-            const uint64_t *kv = &mat[(r + j) * W];
-            if ((kv[tid >> 6] >> (tid & 63)) & 1ull) {
-                int cnt = 0;
+        t = 0;
+        __syncthreads();
+        const bool last = p + 1 == W;
+        if (sm.pivots[p] != 0) {  // workgroup-uniform
+            // 3. the tags; 4. the tables, and the panel's own and the next word
+            const uint32_t pc = sm.pivcol[tid];
+            const bool fresh = (int)(pc >> 6) == p;
+            const int c = (int)(pc & 63u);
+            if (fresh) {
+                used = true;
 #pragma unroll
                 for (int w = 0; w < WMAX; ++w)
-                    if (w < W) cnt += __builtin_popcountll(arow[w] & kv[w]);
-                atomicAdd(&qacc[j], cnt);
+                    if (w >= p && w < W) P.start[w * 64 + c] = row[w];
+            }
+            if (wave == W - 1) fill_tables(P.tau, P.ttab);
+            __syncthreads();
+            uint32_t at[kTabGroups];
+            if (fresh) {
+                t = P.tau[c] ^ (1ull << c);
+            } else if (x) {
+                table_places(x, at);
+                t = table_sum(P.ttab, at);
+            }
+            if (p + wave < W) fill_tables(&P.start[(p + wave) * 64], P.tab + (p + wave) * kTabWords);
+            __syncthreads();
+            if (__ballot(t != 0ull)) {
+                table_places(t, at);
+#pragma unroll
+                for (int w = 0; w < WMAX; ++w)
+                    if (w == p || (w == p + 1 && w < W)) row[w] ^= table_sum(P.tab + w * kTabWords, at);
             }
         }
-    }
-    __syncthreads();
-    if (tid < nk) {
-        const int q = qacc[tid];
-        const int f = freec[tid];
-        if (q & 1) flag_internal = 1;
-        if (q & 2) atomicOr(&shiftw[f >> 6], 1ull << (f & 63));
+        if (last) break;
+#pragma unroll
+        for (int w = 1; w < WMAX; ++w)
+            if (w == p + 1) x = row[w];
+        // the words behind the next panel's own are due, in its step 2
     }
     __syncthreads();
 
-    for (int k = tid; k < n; k += nthr) out.pivots[k] = (k < r) ? piv[k] : -1;
-    for (int idx0 = tid; idx0 < r * W; idx0 += 4 * nthr) {
-        uint64_t v[4];
+    // The reduced rows by pivot column, zero at the other columns, word-major.
+    const uint64_t mine = sm.pivots[wave], lower = (1ull << lane) - 1ull;
+    const bool is_piv = (mine >> lane) & 1ull;
+    if (!is_piv) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int idx = idx0 + u * nthr;
-            const int k = idx / W, w = idx - k * W;
-            v[u] = (idx < r * W) ? rows[piv[k] * W + w] : 0ull;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (idx0 + u * nthr < r * W) out.basis[idx0 + u * nthr] = v[u];
+        for (int w = 0; w < WMAX; ++w)
+            if (w < W) sm.mat[w * ST + tid] = 0ull;
     }
-    if (tid < W) out.shift[tid] = shiftw[tid];
+    if (used) {
+        const int pc = sm.pivcol[tid];
+#pragma unroll
+        for (int w = 0; w < WMAX; ++w)
+            if (w < W) sm.mat[w * ST + pc] = row[w];
+    }
+    // Column tid (its block is `wave`): pivots below it, and the rank.
+    int below = __builtin_popcountll(mine & lower), r = 0;
+    for (int v = 0; v < W; ++v) {
+        const int k = __builtin_popcountll(sm.pivots[v]);
+        if (v < wave) below += k;
+        r += k;
+    }
+    if (tid < n) {
+        if (is_piv) {
+            out.pivots[below] = tid;
+            sm.pivlist[below] = (uint16_t)tid;
+        }
+        if (tid >= r) out.pivots[tid] = -1;
+    }
+    __syncthreads();
+    // B_k = row p_k of A, in consecutive words: loaded here, stored at the end.
+    uint64_t bv[WMAX];
+#pragma unroll
+    for (int k = 0; k < WMAX; ++k) {
+        const int i = i0 + 64 * k;
+        bv[k] = (k < W && i < r) ? rows[(size_t)sm.pivlist[i] * W + w0] : 0ull;
+    }
+
+    // Kernel vectors: entry (c, f) of the reduced rows is entry c of k_f, so
+    // transposing every 64x64 tile in place (pairs (I, J), (J, I) together)
+    // leaves word I of k_f at mat[I][f]; column f of its own block also gets
+    // its bit f.  Words of columns that are not free become 0.
+    for (int d = 0; 2 * d <= W; ++d) {  // tile pairs (I, I + d mod W), wave I
+        const int I = wave, J = wave + d < W ? wave + d : wave + d - W;
+        if (2 * d == W && d && I >= d) break;  // wave J has this pair
+        const uint64_t fI = (64 * I + 64 <= n ? ~0ull : lm) & ~sm.pivots[I];
+        const uint64_t fJ = (64 * J + 64 <= n ? ~0ull : lm) & ~sm.pivots[J];
+        uint64_t ki = 0, kj = 0;
+        if (fJ) ki = wave_transpose64(sm.mat[J * ST + 64 * I + lane]);       // word I of k_{64J + lane}
+        if (fI && d) kj = wave_transpose64(sm.mat[I * ST + 64 * J + lane]);  // word J of k_{64I + lane}
+        if (d == 0) ki |= 1ull << lane;
+        if (!((fJ >> lane) & 1ull)) ki = 0;
+        if (!((fI >> lane) & 1ull)) kj = 0;
+        sm.mat[I * ST + 64 * J + lane] = ki;
+        if (d) sm.mat[J * ST + 64 * I + lane] = kj;
+    }
+    __syncthreads();
+    const bool is_free = tid < n && !is_piv;
+    if (out.kernel && is_free) {
+        const int j = tid - below;
+#pragma unroll
+        for (int w = 0; w < WMAX; ++w)
+            if (w < W) out.kernel[(size_t)j * W + w] = sm.mat[w * ST + tid];
+    }
+
+    // q(k_f) = k_f^T A k_f over the integers = 2 (entries of A below the
+    // diagonal between members of k_f) + (its members on the diagonal).  Wave
+    // v takes rows 64v + lane: their words left of the diagonal against k_f,
+    // the parity over its members among them.
+    {
+        uint64_t a[WMAX];
+        bool loaded = false;
+        const uint64_t dw = sm.diag[wave];
+        for (int J = 0; J < W; ++J) {
+            const uint64_t own = sm.mat[wave * ST + 64 * J + lane];  // this wave's word of k_{64J + lane}
+            uint64_t todo = __ballot(own != 0ull);
+            if (todo && !loaded) {
+                loaded = true;
+#pragma unroll
+                for (int w = 0; w < WMAX; ++w) {
+                    a[w] = (tid < n && w <= wave) ? rows[(size_t)tid * W + w] : 0ull;
+                    if (w == wave) a[w] &= lower;
+                }
+            }
+            for (; todo; todo &= todo - 1) {
+                const int f = __builtin_ctzll(todo);
+                const uint64_t members = readlane64(own, f);
+                // Words 0 .. wave of k_f, one per lane; most are zero for
+                // sparse kernel vectors.
+                const uint64_t kw = lane <= wave ? sm.mat[lane * ST + 64 * J + f] : 0ull;
+                const uint32_t set = (uint32_t)__ballot(kw != 0ull);
+                uint64_t acc = 0;
+#pragma unroll
+                for (int w = 0; w < WMAX; ++w)
+                    if ((set >> w) & 1u) acc ^= a[w] & readlane64(kw, w);
+                const uint64_t odd = __ballot(__builtin_popcountll(acc) & 1) & members;
+                const int q = 2 * (__builtin_popcountll(odd) & 1) + __builtin_popcountll(members & dw);
+                if (lane == 0 && q) atomicAdd(&sm.qacc[64 * J + f], q);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < WMAX; ++k)
+        if (k < W && i0 + 64 * k < r) out.basis[tid + k * nthr] = bv[k];
+    __syncthreads();
+    {
+        const int q = is_free ? sm.qacc[tid] : 0;
+        const uint64_t sw = __ballot(q & 2);
+        if (lane == 0) out.shift[wave] = sw;
+        if (q & 1) sm.internal = 1;
+    }
+    __syncthreads();
     if (tid == 0) {
         *out.rank = r;
-        *out.status = flag_internal ? HLF_EINTERNAL : HLF_OK;
+        *out.status = sm.internal ? HLF_EINTERNAL : HLF_OK;
     }
 }
 

@@ -73,26 +73,73 @@ __device__ __forceinline__ uint64_t wave_xor_u64(uint64_t v) {
     return v;
 }
 
-// 64x64 bit transpose across one wavefront: lane l holds row l (bit c =
-// column c) and gets column l (bit r = row r).  Step j swaps, between lanes l
-// and l ^ j, the bits whose row and column indices differ in bit j, so after
-// the six steps bit (r, c) sits at (r ^ d, c ^ d), d = r ^ c, i.e. at (c, r).
-// Needs all lanes active.
-__device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
+// 32x32 bit transposes within each half of the wave, on the VALU alone:
+// lane l of a half holds row l of each matrix and gets its column l.  Step j
+// exchanges, between lanes l and l ^ j, the bits whose row and column indices
+// differ in bit j (the lane with bit j clear keeps the columns with bit j
+// clear and takes its partner's, moved up by j; the other keeps the columns
+// with bit j set and takes its partner's, moved down).  Partners: j = 16 by
+// a permlane16 swap of the two rows of 16, j = 8 by a row mirror then a half
+// mirror, j = 4 by a half mirror then a quad mirror, j = 2 and 1 by quad
+// permutations (DPP).  Byte and halfword steps merge with one byte permute,
+// the others with a masked rotate and an and-or.
+template <int N>
+__device__ __forceinline__ void half_transpose32_n(uint32_t (&x)[N]) {
     const int lane = (int)(threadIdx.x & (kWave - 1));
+    {   // j = 16: after the swap, the first result holds the lane's own value
+        // in rows 0 and 2 and its partner's in rows 1 and 3, the second the
+        // other way round, so one byte permute with a per-row selector merges
+        const bool up = lane & 16;
+        const uint32_t sel = up ? 0x07060302u : 0x05040100u;
 #pragma unroll
-    for (int step = 5; step >= 0; --step) {
-        const int j = 1 << step;
-        const uint64_t m = j == 32 ? 0x00000000FFFFFFFFull
-                         : j == 16 ? 0x0000FFFF0000FFFFull
-                         : j == 8  ? 0x00FF00FF00FF00FFull
-                         : j == 4  ? 0x0F0F0F0F0F0F0F0Full
-                         : j == 2  ? 0x3333333333333333ull
-                                   : 0x5555555555555555ull;
-        const uint64_t y = __shfl_xor(x, j, kWave);
-        x = (lane & j) ? ((x & ~m) | ((y & ~m) >> j)) : ((x & m) | ((y & m) << j));
+        for (int i = 0; i < N; ++i) {
+            const auto sw = __builtin_amdgcn_permlane16_swap(x[i], x[i], false, false);
+            x[i] = __builtin_amdgcn_perm(sw[1], sw[0], sel);
+        }
     }
-    return x;
+    {   // j = 8
+        const uint32_t sel = (lane & 8) ? 0x03070105u : 0x06020400u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int t = __builtin_amdgcn_mov_dpp((int)x[i], 0x140, 0xF, 0xF, false);   // row mirror
+            const uint32_t y = (uint32_t)__builtin_amdgcn_mov_dpp(t, 0x141, 0xF, 0xF, false);  // half mirror
+            x[i] = __builtin_amdgcn_perm(y, x[i], sel);
+        }
+    }
+#pragma unroll
+    for (int step = 2; step >= 0; --step) {
+        const int j = 1 << step;
+        const uint32_t mj = j == 4 ? 0x0F0F0F0Fu : j == 2 ? 0x33333333u : 0x55555555u;
+        const uint32_t M = (lane & j) ? ~mj : mj;
+        const uint32_t R = (lane & j) ? (uint32_t)j : (uint32_t)(32 - j);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            int y;
+            if (j == 4) {
+                const int t = __builtin_amdgcn_mov_dpp((int)x[i], 0x141, 0xF, 0xF, false);  // half mirror
+                y = __builtin_amdgcn_mov_dpp(t, 0x1B, 0xF, 0xF, true);                     // quad [3,2,1,0]
+            } else if (j == 2) {
+                y = __builtin_amdgcn_mov_dpp((int)x[i], 0x4E, 0xF, 0xF, true);  // quad [2,3,0,1]
+            } else {
+                y = __builtin_amdgcn_mov_dpp((int)x[i], 0xB1, 0xF, 0xF, true);  // quad [1,0,3,2]
+            }
+            const uint32_t t = (uint32_t)y & M;
+            x[i] = (x[i] & M) | __builtin_amdgcn_alignbit(t, t, R);
+        }
+    }
+}
+
+// 64x64 bit transpose across one wavefront: lane l holds row l (bit c =
+// column c) and gets column l (bit r = row r).  Each half of the wave
+// transposes its two 32x32 blocks; one swap of the low dwords of the upper
+// half with the high dwords of the lower half exchanges the off-diagonal ones
+// (33 VALU instructions; by lane shuffles through LDS it takes twelve of them
+// in a chain).  Needs all lanes active.
+__device__ __forceinline__ uint64_t wave_transpose64(uint64_t x) {
+    uint32_t d[2] = {(uint32_t)x, (uint32_t)(x >> 32)};
+    half_transpose32_n<2>(d);
+    const auto sw = __builtin_amdgcn_permlane32_swap(d[0], d[1], false, false);
+    return ((uint64_t)sw[1] << 32) | sw[0];
 }
 
 // Orders the LDS accesses of one wavefront around this point (waits for its
