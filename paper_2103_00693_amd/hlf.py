@@ -117,12 +117,15 @@ def words_for(n: int) -> int:
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The stream's handle.  torch.cuda.current_stream() makes a Stream object
+    first, 2.7 us of a call that takes 7.5 us with it and 4.7 us without."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _check(code: int, where: str):
