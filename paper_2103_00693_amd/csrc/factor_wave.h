@@ -2,15 +2,26 @@
 // instance with n <= 64*WMAX (WMAX in {1,2,3}) on one wavefront.
 //
 // Lane l holds rows l, l+64, l+128 ("slots") in VGPRs.  Gauss-Jordan over
-// GF(2) takes a ballot per slot to find the candidate rows of a column, picks
-// the lowest, broadcasts it with readlane and XORs it into every other row
-// that has the column set -- no barriers, no LDS in the elimination.  The
-// reduced rows then give the Ker(A) basis (task (2)), q on it (task (3)) and
-// the canonical shift (task (4)).
+// GF(2), column by column: a ballot per slot finds the rows with the column
+// set, readlane broadcasts one, and it is XORed into every row that has the
+// column -- itself included, which takes it off the list -- and kept in a
+// second set of registers, the reduced pivot rows, under the lane and slot
+// of its column, where later columns are eliminated the same way.  No
+// barrier, no LDS.  Those registers, transposed across the wave, are the
+// Ker(A) basis (task (2)); q on it (task (3)) and the canonical shift (task
+// (4)) take one uniform step per free column.
+//
+// Bound by one wave's chain of instructions, which issue one in about five
+// cycles: some 175 cycles a column at n <= 64 (425 with the candidates, the
+// rank and the lists kept per lane and in LDS), 0.8 us to read A (1.6 us at
+// n = 16 and 4.8 at n = 64 with one byte per lane and load).  The whole of a
+// small solve is 9.0 k cycles at n = 16 (15.8 k) and 18.2 k at n = 64 (42.1 k).
 //
 // Only the calling wave takes part (LDS ordering by wave_lds_sync), so the
 // routine can run on one wave of a larger workgroup.
 #pragma once
+
+#include <type_traits>
 
 #include "hlf_device.h"
 #include "hlf_internal.h"
@@ -19,20 +30,11 @@ namespace hlf {
 
 template <int WMAX>
 struct WaveSmem {
-    uint64_t orig[64 * WMAX * WMAX];  // A, packed rows of W words
-    uint64_t rref[64 * WMAX * WMAX];  // RREF row k at k*W
+    uint64_t orig[64 * WMAX * WMAX];           // A, packed rows of W words
+    uint32_t stream[128 * WMAX * WMAX + 2];    // A's entries, one bit each, row after row
     int piv[64 * WMAX];
-    int freec[64 * WMAX];
     unsigned long long shiftw[WMAX];
-    int internal;
 };
-
-template <int WMAX>
-__device__ __forceinline__ void set_bit(uint64_t (&v)[WMAX], int pos) {
-#pragma unroll
-    for (int w = 0; w < WMAX; ++w)
-        if (w == (pos >> 6)) v[w] |= 1ull << (pos & 63);
-}
 
 // Packed rows from global memory into sm.orig.
 template <int WMAX>
@@ -41,79 +43,91 @@ __device__ __forceinline__ void wave_load_rows(const uint64_t *__restrict__ rows
     for (int idx = lane_id(); idx < n * W; idx += 64) sm.orig[idx] = rows[idx];
 }
 
-// Dense row-major uint8 matrix into sm.orig: lane l reads column 64*w + l of
-// 16 rows at once (independent loads, one memory latency per group), and the
-// ballot over the 64 lanes of each row gives its packed word.  Returns true
-// on every lane if an entry is not 0/1.
+// Dense row-major uint8 matrix into sm.orig: 16 consecutive entries per lane
+// and load, at any address, kBatch loads in flight; each becomes 16 bits of
+// the stream, and lane i then cuts rows i, i + 64, .. out of it.  The last
+// load ends with the matrix and is shifted into place.  Four 0/1 bytes x
+// become four bits as (x * 0x10204080) >> 28 (no carries reach bits 28..31).
+// Returns true on every lane if an entry is not 0/1.
 template <int WMAX>
 __device__ __forceinline__ bool wave_load_dense(const uint8_t *__restrict__ A, int n, int W,
                                                 WaveSmem<WMAX> &sm) {
-    constexpr int G = 16;
+    typedef u32x4 quad_any __attribute__((aligned(1)));
+    constexpr int kBatch = WMAX == 1 ? 4 : 9;
     const int lane = lane_id();
+    const int nn = n * n;
+    uint16_t *s16 = reinterpret_cast<uint16_t *>(sm.stream);
     bool bad = false;
-    for (int w = 0; w < W; ++w) {
-        const int j = 64 * w + lane;
-        const bool jin = j < n;
-        for (int i0 = 0; i0 < n; i0 += G) {
-            uint32_t v[G];
+    if (nn < 16) {
+        const uint32_t v = lane < nn ? (uint32_t)A[lane] : 0u;
+        bad = v > 1u;
+        const uint64_t bits = __ballot(v == 1u);
+        if (lane == 0) sm.stream[0] = (uint32_t)bits;
+    } else {
+        for (int q0 = 0; 16 * q0 < nn; q0 += 64 * kBatch) {
+            u32x4 v[kBatch];
 #pragma unroll
-            for (int k = 0; k < G; ++k)
-                v[k] = (jin && i0 + k < n) ? (uint32_t)A[(size_t)(i0 + k) * n + j] : 0u;
+            for (int k = 0; k < kBatch; ++k) {
+                const int at = min(16 * (q0 + 64 * k + lane), nn - 16);
+                v[k] = *reinterpret_cast<const quad_any *>(A + at);
+            }
 #pragma unroll
-            for (int k = 0; k < G; ++k) {
-                if (i0 + k >= n) break;
-                bad |= v[k] > 1u;
-                const uint64_t word = __ballot(v[k] == 1u);
-                if (lane == 0) sm.orig[(i0 + k) * W + w] = word;
+            for (int k = 0; k < kBatch; ++k) {
+                const int q = q0 + 64 * k + lane;
+                bad |= ((v[k].x | v[k].y | v[k].z | v[k].w) & 0xFEFEFEFEu) != 0;
+                const uint32_t bits = (v[k].x * 0x10204080u) >> 28 | (v[k].y * 0x10204080u) >> 28 << 4 |
+                                      (v[k].z * 0x10204080u) >> 28 << 8 | (v[k].w * 0x10204080u) >> 28 << 12;
+                if (16 * q < nn) s16[q] = (uint16_t)(bits >> max(16 * q + 16 - nn, 0));
+            }
+        }
+    }
+    wave_lds_sync();
+    const uint64_t lm = last_word_mask(n);
+#pragma unroll
+    for (int s = 0; s < WMAX; ++s) {
+        const int i = 64 * s + lane;
+        if (i < n) {
+#pragma unroll
+            for (int w = 0; w < WMAX; ++w) {
+                if (w >= W) break;
+                const int bit = i * n + 64 * w, d = bit >> 5, sh = bit & 31;  // words past the stream: masked off
+                const uint32_t a = sm.stream[d], b = sm.stream[d + 1], c = sm.stream[d + 2];
+                const uint64_t v = (uint64_t)__builtin_amdgcn_alignbit(c, b, sh) << 32 |
+                                   (uint32_t)__builtin_amdgcn_alignbit(b, a, sh);
+                sm.orig[i * W + w] = w == W - 1 ? v & lm : v;
             }
         }
     }
     return __ballot(bad) != 0;
 }
 
-// Factor the matrix in sm.orig.  `bad_input` forces HLF_ENOTSYM.  Returns the
-// rank, or -1 if the record was marked invalid.
-template <int WMAX>
-__device__ int factor_wave_core(int n, int W, bool bad_input, const FactorOut &out,
-                                WaveSmem<WMAX> &sm) {
+// The elimination for exactly W words a row.
+template <int W, class Smem>
+__device__ int factor_wave_words(int n, bool bad_input, const FactorOut &out, Smem &sm) {
     const int lane = lane_id();
-    if (lane < WMAX) sm.shiftw[lane] = 0;
-    if (lane == 0) sm.internal = 0;
+    const uint64_t below = (1ull << lane) - 1ull;
     wave_lds_sync();
-
-    uint64_t row[WMAX][WMAX];
-    bool used[WMAX];
-    int rk[WMAX], pc[WMAX];  // rank and pivot column of a pivot row
-#pragma unroll
-    for (int s = 0; s < WMAX; ++s) {
-        const int i = s * 64 + lane;
-#pragma unroll
-        for (int w = 0; w < WMAX; ++w) row[s][w] = (i < n && w < W) ? sm.orig[i * W + w] : 0ull;
-        used[s] = false;
-        rk[s] = -1;
-        pc[s] = -1;
-    }
-
-    // Validation: pad bits zero, A = A^T (slot s of word cw, transposed across
-    // the wave, gives lane l word s of column 64cw + l, which must equal word
-    // s of row 64cw + l).
+    uint32_t x[W][2 * W];  // rows, as dwords
     bool bad = bad_input;
-    const uint64_t lm = last_word_mask(n);
+    {
+        uint64_t row[W][W];
 #pragma unroll
-    for (int s = 0; s < WMAX; ++s)
+        for (int s = 0; s < W; ++s) {
+            const int i = s * 64 + lane;
 #pragma unroll
-        for (int w = 0; w < WMAX; ++w)
-            if (w == W - 1 && (row[s][w] & ~lm)) bad = true;
-#pragma unroll
-    for (int cw = 0; cw < WMAX; ++cw) {
-        if (cw >= W) break;
-        const int c = 64 * cw + lane;
-#pragma unroll
-        for (int s = 0; s < WMAX; ++s) {
-            if (s >= W) break;
-            const uint64_t col = wave_transpose64(row[s][cw]);
-            if (c < n && col != sm.orig[c * W + s]) bad = true;
+            for (int w = 0; w < W; ++w) {
+                row[s][w] = i < n ? sm.orig[i * W + w] : 0ull;
+                x[s][2 * w] = (uint32_t)row[s][w];
+                x[s][2 * w + 1] = (uint32_t)(row[s][w] >> 32);
+            }
+            if (row[s][W - 1] & ~last_word_mask(n)) bad = true;  // pad bits
         }
+        // A = A^T, tile pair by tile pair
+#pragma unroll
+        for (int s = 0; s < W; ++s)
+#pragma unroll
+            for (int w = s; w < W; ++w)
+                if (wave_transpose64(row[s][w]) != row[w][s]) bad = true;
     }
     if (__ballot(bad)) {
         if (lane == 0) {
@@ -123,147 +137,153 @@ __device__ int factor_wave_core(int n, int W, bool bad_input, const FactorOut &o
         return -1;
     }
 
-    // Gauss-Jordan over GF(2), column by column.
-    int r = 0, nfree = 0;
+    // Column c: a row that has it, px, is XORed into every row and every
+    // pivot row that has it.  Words left of the column are zero in px.
+    uint32_t p[W][2 * W];  // pivot rows: that of column 64s + l in slot s, lane l
+    uint64_t pivots[W];    // columns that have one
 #pragma unroll
-    for (int cw = 0; cw < WMAX; ++cw) {
-        if (cw >= W) break;
-        for (int cb = 0; cb < 64; ++cb) {
-            const int c = 64 * cw + cb;
-            if (c >= n) break;
-            int ps = -1, pl = 0;
+    for (int s = 0; s < W; ++s) {
+        pivots[s] = 0;
 #pragma unroll
-            for (int s = 0; s < WMAX; ++s) {
-                const bool cand = (s < W) && !used[s] && ((row[s][cw] >> cb) & 1ull);
-                const uint64_t m = __ballot(cand);
-                if (ps < 0 && m) {
-                    ps = s;
-                    pl = __builtin_ctzll(m);
+        for (int d = 0; d < 2 * W; ++d) p[s][d] = 0;
+    }
+#pragma unroll
+    for (int h = 0; h < 2 * W; ++h) {
+        const int cols = min(32, n - 32 * h);
+        uint32_t found = 0;
+        for (int b = 0; b < cols; ++b) {
+            uint32_t m[W];
+            uint64_t has[W], any = 0;
+#pragma unroll
+            for (int s = 0; s < W; ++s) {
+                m[s] = (uint32_t)__builtin_amdgcn_sbfe((int)x[s][h], b, 1);
+                has[s] = __ballot(m[s] != 0u);
+                any |= has[s];
+            }
+            if (any == 0) continue;  // a free column
+            uint32_t px[2 * W];
+            auto take = [&](auto slot) {  // a branch per slot: merged, they would index x in memory
+                constexpr int s = decltype(slot)::value;
+                if constexpr (W > 1) asm volatile("; slot %0" ::"n"(s));
+                const int at = __builtin_ctzll(has[s]);
+#pragma unroll
+                for (int d = h; d < 2 * W; ++d) px[d] = (uint32_t)__builtin_amdgcn_readlane((int)x[s][d], at);
+            };
+            if (W == 1 || has[0] != 0)
+                take(std::integral_constant<int, 0>{});
+            else if (W == 2 || has[1 % W] != 0)
+                take(std::integral_constant<int, 1 % W>{});
+            else
+                take(std::integral_constant<int, 2 % W>{});
+            found |= 1u << b;
+#pragma unroll
+            for (int s = 0; s < W; ++s)
+#pragma unroll
+                for (int d = h; d < 2 * W; ++d) x[s][d] = __builtin_amdgcn_bitop3_b32(x[s][d], m[s], px[d], 0x78);
+            const bool mine = lane == 32 * (h & 1) + b;
+#pragma unroll
+            for (int s = 0; s <= h / 2; ++s) {
+                const uint32_t mp = (uint32_t)__builtin_amdgcn_sbfe((int)p[s][h], b, 1);
+#pragma unroll
+                for (int d = h; d < 2 * W; ++d) {
+                    const uint32_t v = __builtin_amdgcn_bitop3_b32(p[s][d], mp, px[d], 0x78);
+                    p[s][d] = s == h / 2 && mine ? px[d] : v;
                 }
             }
-            if (ps < 0) {
-                if (lane == 0) sm.freec[nfree] = c;
-                ++nfree;
-                continue;
+        }
+        pivots[h >> 1] |= (uint64_t)found << (32 * (h & 1));
+    }
+
+    int r = 0;
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+        const int c = 64 * s + lane, k = r + __builtin_popcountll(pivots[s] & below);
+        if ((pivots[s] >> lane) & 1ull) {
+            sm.piv[k] = c;
+            out.pivots[k] = c;
+#pragma unroll
+            for (int w = 0; w < W; ++w) out.basis[k * W + w] = sm.orig[c * W + w];
+        }
+        r += __builtin_popcountll(pivots[s]);
+    }
+    for (int k = r + lane; k < n; k += 64) out.pivots[k] = -1;
+    // Lane f of the transposed pivot rows holds column f, whose bit c is entry
+    // f of column c's pivot row: k_f = e_f | column f.
+    uint64_t shiftbits[W];
+    bool internal = false;
+#pragma unroll
+    for (int t = 0; t < W; ++t) shiftbits[t] = 0;
+    if (r < n) {
+        uint64_t a[W][W];  // A again
+#pragma unroll
+        for (int s = 0; s < W; ++s)
+#pragma unroll
+            for (int w = 0; w < W; ++w) a[s][w] = 64 * s + lane < n ? sm.orig[(64 * s + lane) * W + w] : 0ull;
+        int before = 0;  // free columns of the words before
+#pragma unroll
+        for (int t = 0; t < W; ++t) {
+            const uint64_t cols = 64 * t + 64 <= n ? ~0ull : 64 * t < n ? (1ull << (n & 63)) - 1ull : 0ull;
+            const uint64_t free = cols & ~pivots[t];
+            if (free == 0) continue;
+            const bool is_free = (free >> lane) & 1ull;
+            uint64_t kv[W];
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                kv[u] = wave_transpose64((uint64_t)p[u][2 * t + 1] << 32 | p[u][2 * t]);
+                if (u == t) kv[u] |= 1ull << lane;
             }
-            pl = __builtin_amdgcn_readfirstlane(pl);
-            uint64_t prow[WMAX];
+            if (out.kernel && is_free) {
+                const int j = before + __builtin_popcountll(free & below);
 #pragma unroll
-            for (int w = 0; w < WMAX; ++w) prow[w] = 0;
+                for (int u = 0; u < W; ++u) out.kernel[j * W + u] = kv[u];
+            }
+            before += __builtin_popcountll(free);
+            // q(k_f) = sum over i in supp k_f of popcount(A_i & k_f): every
+            // term is even (A k_f = 0 mod 2), so bit 1 of the sum is the
+            // parity of the terms = 2 mod 4.
+            for (uint64_t fm = free; fm; fm &= fm - 1ull) {
+                const int f = __builtin_ctzll(fm);
+                uint64_t k[W];
 #pragma unroll
-            for (int s = 0; s < WMAX; ++s)
-                if (s == ps)
+                for (int u = 0; u < W; ++u) k[u] = readlane64(kv[u], f);
+                uint32_t twos = 0, ones = 0;
 #pragma unroll
-                    for (int w = 0; w < WMAX; ++w) prow[w] = readlane64(row[s][w], pl);
+                for (int s = 0; s < W; ++s) {
+                    uint32_t term = 0;
 #pragma unroll
-            for (int s = 0; s < WMAX; ++s) {
-                const bool is_p = (s == ps) && (lane == pl);
-                if (((row[s][cw] >> cb) & 1ull) && !is_p)
-#pragma unroll
-                    for (int w = 0; w < WMAX; ++w) row[s][w] ^= prow[w];
-                if (is_p) {
-                    used[s] = true;
-                    rk[s] = r;
-                    pc[s] = c;
+                    for (int u = 0; u < W; ++u) term += (uint32_t)__builtin_popcountll(a[s][u] & k[u]);
+                    if (!((k[s] >> lane) & 1ull)) term = 0;
+                    twos ^= term;
+                    ones |= term;
                 }
+                if (__ballot(ones & 1u)) internal = true;
+                if (__builtin_popcountll(__ballot(twos & 2u)) & 1) shiftbits[t] |= 1ull << f;
             }
-            if (lane == 0) sm.piv[r] = c;
-            ++r;
         }
     }
-    if constexpr (WMAX == 1) {
-        // One word per row (n <= 64).  P[c] = the reduced pivot row whose
-        // pivot column is c, 0 at free columns; transposed across the wave,
-        // lane f holds column f of P, whose bit c is that row's entry f, so
-        // k_f = e_f | column f of P for a free column f.
-        sm.rref[lane] = 0ull;
-        wave_lds_sync();
-        if (used[0]) sm.rref[pc[0]] = row[0][0];
-        wave_lds_sync();
-        const uint64_t P = sm.rref[lane];
-        if (lane < n) out.pivots[lane] = (lane < r) ? sm.piv[lane] : -1;
-        if (lane < r) out.basis[lane] = sm.orig[sm.piv[lane]];
-        const uint64_t pivmask = __ballot(P != 0ull);  // a pivot row is never 0
-        const uint64_t freemask = __ballot(lane < n) & ~pivmask;
-        const bool is_free = (freemask >> lane) & 1ull;
-        const uint64_t T = wave_transpose64(P);  // every lane takes part in the exchanges
-        const uint64_t kv = is_free ? (T | (1ull << lane)) : 0ull;
-        if (out.kernel && is_free) out.kernel[__builtin_popcountll(freemask & ((1ull << lane) - 1ull))] = kv;
-        // q(k_f) = sum over i in supp k_f of popcount(A_i & k_f), one uniform
-        // step per free column: every term is even (A k_f = 0 mod 2), so bit
-        // 1 of the sum is the parity of the terms = 2 mod 4.
-        const uint64_t Ai = lane < n ? sm.orig[lane] : 0ull;
-        uint64_t shiftbits = 0ull;
-        bool internal = false;
-        for (uint64_t fm = freemask; fm; fm &= fm - 1ull) {
-            const int f = __builtin_ctzll(fm);
-            const uint64_t x = readlane64(kv, f);
-            const uint32_t term = ((x >> lane) & 1ull) ? (uint32_t)__builtin_popcountll(Ai & x) : 0u;
-            if (__ballot(term & 1u)) internal = true;
-            if (__builtin_popcountll(__ballot(term & 2u)) & 1) shiftbits |= 1ull << f;
+    if (lane == 0) {
+#pragma unroll
+        for (int t = 0; t < W; ++t) {
+            sm.shiftw[t] = shiftbits[t];
+            out.shift[t] = shiftbits[t];
         }
-        if (lane == 0) sm.shiftw[0] = shiftbits;
-        wave_lds_sync();
-        if (lane == 0) {
-            out.shift[0] = shiftbits;
-            *out.rank = r;
-            *out.status = internal ? HLF_EINTERNAL : HLF_OK;
-        }
-        return internal ? -1 : r;
-    } else {
-#pragma unroll
-        for (int s = 0; s < WMAX; ++s)
-            if (used[s])
-#pragma unroll
-                for (int w = 0; w < WMAX; ++w)
-                    if (w < W) sm.rref[rk[s] * W + w] = row[s][w];
-        wave_lds_sync();
-
-        for (int k = lane; k < n; k += 64) out.pivots[k] = (k < r) ? sm.piv[k] : -1;
-        for (int idx = lane; idx < r * W; idx += 64) {
-            const int k = idx / W, w = idx - k * W;
-            out.basis[idx] = sm.orig[sm.piv[k] * W + w];
-        }
-
-        // Kernel vectors k_f and q(k_f) = sum_{i in supp k_f} popcount(A_i & k_f).
-        const int nk = n - r;
-        for (int j = lane; j < nk; j += 64) {
-            const int f = sm.freec[j];
-            uint64_t kv[WMAX];
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w) kv[w] = 0;
-            set_bit<WMAX>(kv, f);
-            for (int k = 0; k < r; ++k) {
-                if ((sm.rref[k * W + (f >> 6)] >> (f & 63)) & 1ull) set_bit<WMAX>(kv, sm.piv[k]);
-            }
-            if (out.kernel)
-#pragma unroll
-                for (int w = 0; w < WMAX; ++w)
-                    if (w < W) out.kernel[j * W + w] = kv[w];
-            uint32_t q = 0;
-#pragma unroll
-            for (int iw = 0; iw < WMAX; ++iw) {
-                uint64_t bits = kv[iw];
-                while (bits) {
-                    const int i = iw * 64 + __builtin_ctzll(bits);
-                    bits &= bits - 1;
-#pragma unroll
-                    for (int w = 0; w < WMAX; ++w)
-                        if (w < W) q += __builtin_popcountll(sm.orig[i * W + w] & kv[w]);
-                }
-            }
-            if (q & 1u) sm.internal = 1;
-            if (q & 2u) atomicOr(&sm.shiftw[f >> 6], 1ull << (f & 63));
-        }
-        wave_lds_sync();
-        if (lane < W) out.shift[lane] = sm.shiftw[lane];
-        const bool internal = sm.internal != 0;
-        if (lane == 0) {
-            *out.rank = r;
-            *out.status = internal ? HLF_EINTERNAL : HLF_OK;
-        }
-        return internal ? -1 : r;
+        *out.rank = r;
+        *out.status = internal ? HLF_EINTERNAL : HLF_OK;
     }
+    wave_lds_sync();
+    return internal ? -1 : r;
+}
+
+// Factor the matrix in sm.orig.  `bad_input` forces HLF_ENOTSYM.  Returns the
+// rank, or -1 if the record was marked invalid.
+template <int WMAX>
+__device__ int factor_wave_core(int n, int W, bool bad_input, const FactorOut &out,
+                                WaveSmem<WMAX> &sm) {
+    if constexpr (WMAX >= 3)
+        if (W == 3) return factor_wave_words<3>(n, bad_input, out, sm);
+    if constexpr (WMAX >= 2)
+        if (W == 2) return factor_wave_words<2>(n, bad_input, out, sm);
+    return factor_wave_words<1>(n, bad_input, out, sm);
 }
 
 }  // namespace hlf
