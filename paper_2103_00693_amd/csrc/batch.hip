@@ -296,57 +296,76 @@ __global__ void batch_queue_reset_kernel(QueueHead *q, ChunkSlot *slots, int cou
 }
 
 // Offsets of the batch layout (prefix sums over the instance sizes) for the
-// allocation-free reduce: one workgroup of 1024 threads, count <= 1024 * kPer.
-// An n outside [1, max_n] counts as 0 (no space; its factor task reports
-// HLF_EINVAL).  n_eff receives the sizes the other kernels use.
+// allocation-free reduce, and the queue reset: one workgroup of 1024 threads,
+// count <= 1024 * kLayoutPer.  An n outside [1, max_n] counts as 0 (no space;
+// its factor task reports HLF_EINVAL).  n_eff receives the sizes the other
+// kernels use.  Every sum fits 32 bits (16384 * 192^2 < 2^30).  54 sizes took
+// 8.7 us and the reset another launch of 4.6, with 16 sizes a thread, one
+// after the other, and ten rounds of a scan over LDS.
 constexpr int kLayoutPer = 16;
 
 __global__ __launch_bounds__(1024) void noalloc_layout_kernel(const int32_t *__restrict__ n_in,
                                                               int count, int max_n, int32_t *n_eff,
                                                               int64_t *dense_off, int64_t *mat_off,
-                                                              int64_t *vec_off, int64_t *piv_off) {
-    __shared__ int64_t part[4][1024];
-    const int t = threadIdx.x;
-    const int i0 = t * kLayoutPer;
-    int64_t loc[4] = {0, 0, 0, 0};
-    for (int i = i0; i < min(count, i0 + kLayoutPer); ++i) {
-        const int n = n_in[i];
-        const int64_t ne = (n >= 1 && n <= max_n) ? n : 0;
-        const int64_t W = (ne + 63) >> 6;
-        loc[0] += ne * ne;
-        loc[1] += ne * W;
-        loc[2] += W;
-        loc[3] += ne;
+                                                              int64_t *vec_off, int64_t *piv_off,
+                                                              QueueHead *q, ChunkSlot *slots) {
+    __shared__ uint32_t part[16][4];
+    const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+    const int per = (count + 1023) >> 10;
+    const int i0 = t * per, i1 = min(count, i0 + per);
+    for (int i = t; i < count; i += 1024) slots[i].entry = 0;
+    if (t == 0) {
+        q->fnext = 0;
+        q->fdone = 0;
+        q->cnext = 0;
+        q->claim = 0;
     }
+    auto sizes = [&](int i, uint32_t (&v)[4]) {
+        const int n = n_in[i];
+        const uint32_t ne = (n >= 1 && n <= max_n) ? (uint32_t)n : 0u, W = (ne + 63) >> 6;
+        v[0] = ne * ne;
+        v[1] = ne * W;
+        v[2] = W;
+        v[3] = ne;
+    };
+    uint32_t loc[4] = {0, 0, 0, 0};
+    for (int i = i0; i < i1; ++i) {
+        uint32_t v[4];
+        sizes(i, v);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) part[q][t] = loc[q];
+        for (int k = 0; k < 4; ++k) loc[k] += v[k];
+    }
+    uint32_t run[4];  // inclusive over the wave, then exclusive over all
+#pragma unroll
+    for (int k = 0; k < 4; ++k) run[k] = loc[k];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t up = (uint32_t)__shfl_up((int)run[k], d);
+            if (lane >= d) run[k] += up;
+        }
+    }
+    if (lane == 63) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part[wave][k] = run[k];
+    }
     __syncthreads();
-    // inclusive scan over the 1024 partial sums (Hillis-Steele)
-    for (int d = 1; d < 1024; d <<= 1) {
-        int64_t v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = t >= d ? part[q][t - d] : 0;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) part[q][t] += v[q];
-        __syncthreads();
+    for (int k = 0; k < 4; ++k) {
+        run[k] -= loc[k];
+        for (int v = 0; v < wave; ++v) run[k] += part[v][k];
     }
-    int64_t run[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) run[q] = part[q][t] - loc[q];  // exclusive
-    for (int i = i0; i < min(count, i0 + kLayoutPer); ++i) {
-        const int n = n_in[i];
-        const int64_t ne = (n >= 1 && n <= max_n) ? n : 0;
-        const int64_t W = (ne + 63) >> 6;
-        n_eff[i] = (int32_t)ne;
+    for (int i = i0; i < i1; ++i) {
+        uint32_t v[4];
+        sizes(i, v);
+        n_eff[i] = (int32_t)v[3];
         dense_off[i] = run[0];
         mat_off[i] = run[1];
         vec_off[i] = run[2];
         piv_off[i] = run[3];
-        run[0] += ne * ne;
-        run[1] += ne * W;
-        run[2] += W;
-        run[3] += ne;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) run[k] += v[k];
     }
 }
 
@@ -396,13 +415,23 @@ __device__ void reduce_chunk(const BatchDev &b, int inst, int r, unsigned long l
 
 template <int WMAX>
 __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint8_t *__restrict__ A,
-                                                          int max_rank, int chunk_log2,
+                                                          int max_rank, int chunk_log2, int drawn,
                                                           QueueHead *q, ChunkSlot *slots) {
     __shared__ WaveSmem<WMAX> sm;
     const int lane = lane_id();
 
-    // Phase 1: factor tasks.
-    for (;;) {
+    // Phase 1: factor tasks.  Drawn, the first one too: a wave that is not
+    // running yet must not hold one that running waves wait for.  Draws come
+    // one in 12 ns and hold up all other accesses meanwhile (2048 waves: 24 us
+    // before the first task was done), so waves beyond the number of tasks let
+    // the others draw first, and nobody draws once all are taken.
+    for (bool first = true;; first = false) {
+        if (!first || blockIdx.x >= (unsigned int)b.count) {
+            if (first)
+                for (int k = 0; k <= b.count >> 5; ++k) __builtin_amdgcn_s_sleep(16);
+            if ((unsigned int)__builtin_amdgcn_readfirstlane((int)relaxed_load(&q->fnext)) >= (unsigned int)b.count)
+                break;
+        }
         unsigned int f = 0;
         if (lane == 0) f = atomicAdd(&q->fnext, 1u);
         f = (unsigned int)__builtin_amdgcn_readfirstlane((int)f);
@@ -446,7 +475,8 @@ __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint
         __syncthreads();  // LDS is reused by the next factor task
     }
 
-    // Phase 2: chunk tasks, the first one by the wave's index.
+    // Phase 2: chunk tasks, the first one by the wave's index, the others drawn
+    // or, where they are short (see kShortPieceLog2), in turn.
     unsigned long long c = blockIdx.x;
     for (;;) {
         unsigned long long e = 0;
@@ -464,9 +494,9 @@ __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint
                 break;
             }
             // Thousands of waves polling at full rate hold up the atomics that
-            // they wait for: back off to 7 us.
-            if (naps < 4) __builtin_amdgcn_s_sleep(16);
-            else __builtin_amdgcn_s_sleep(127), __builtin_amdgcn_s_sleep(127);
+            // they wait for: back off, with the grid, to 7 us at 2048 waves.
+            const int units = naps < 4 ? 1 : 1 + (int)(gridDim.x >> 7);
+            for (int k = 0; k < units; ++k) __builtin_amdgcn_s_sleep(16);
         }
         if (e == 0) break;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the record behind the entry
@@ -484,9 +514,13 @@ __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint
             if (W == 2) reduce_chunk<2>(b, inst, r, c0, c1);
         if constexpr (WMAX >= 3)
             if (W == 3) reduce_chunk<3>(b, inst, r, c0, c1);
-        unsigned long long next = 0;
-        if (lane == 0) next = atomicAdd(&q->cnext, 1ull);
-        c = gridDim.x + uniform64(next);
+        if (drawn) {
+            unsigned long long next = 0;
+            if (lane == 0) next = atomicAdd(&q->cnext, 1ull);
+            c = gridDim.x + uniform64(next);
+        } else {
+            c += gridDim.x;
+        }
     }
 }
 
@@ -590,9 +624,20 @@ bool claims_fit_count(int count, int max_rank, int chunk_log2) {
 // pieces of 2^17, 6.27 of 2^16, 6.49 of 2^15, where the draws begin to queue).
 constexpr int kPieceLog2 = 17;
 
-int piece_log2(int count, int max_rank, int chunk_log2) {
+// Batches that cannot hold that many solutions for every wave take shorter
+// pieces, an eighth of what a wave could get at most, down to 2^12: an
+// instance of rank 16 is then the work of 16 waves instead of one, 2 us
+// instead of 37.  Draws come one in 9 ns at best, so waves take short pieces
+// in turn, without.
+constexpr int kShortPieceLog2 = 12;
+
+int piece_log2(int count, int max_rank, int chunk_log2, int grid) {
+    int most = max_rank;  // log2 of the solutions per wave, at most
+    for (int c = count; c > grid; c >>= 1) ++most;
+    for (int c = count; c < grid; c <<= 1) --most;
+    const int want = std::min(kPieceLog2, std::max(kShortPieceLog2, most - 3));
     int p = chunk_log2;
-    while (p > kPieceLog2 && claims_fit_count(count, max_rank, p - 1)) --p;
+    while (p > want && claims_fit_count(count, max_rank, p - 1)) --p;
     return p;
 }
 
@@ -600,8 +645,8 @@ bool claims_fit(const hlf_batch_s *b, int max_rank, int chunk_log2) {
     return claims_fit_count(b->count, max_rank, chunk_log2);
 }
 
-// Queue reset + the persistent factor/reduce kernel over the instances of a
-// device view, with the given queue and slot arrays.
+// The persistent factor/reduce kernel over the instances of a device view,
+// with the given queue and slot arrays, which have been reset.
 template <int WMAX>
 hlf_status launch_reduce_view(const hlf::BatchDev &d, const uint8_t *A, int max_rank,
                               const hlf_batch_params &p, hlf::QueueHead *queue,
@@ -612,19 +657,22 @@ hlf_status launch_reduce_view(const hlf::BatchDev &d, const uint8_t *A, int max_
         per_cu < 1)
         per_cu = 1;
     const int waves = std::min(p.waves_per_cu, per_cu);
-    const int grid = hlf::device_cu_count() * waves;
-    const int reset_blocks = (d.count + 255) / 256;
-    hipLaunchKernelGGL(hlf::batch_queue_reset_kernel, dim3(reset_blocks), dim3(256), 0, stream,
-                       queue, slots, d.count);
-    if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, d, A, max_rank,
-                       piece_log2(d.count, max_rank, p.chunk_log2), queue, slots);
+    int grid = hlf::device_cu_count() * waves;
+    const int piece = piece_log2(d.count, max_rank, p.chunk_log2, grid);
+    // no more waves than factor tasks or pieces there can be
+    const int e = std::max(max_rank - piece, 0);
+    if (e < 20 && (int64_t)d.count << e < grid) grid = d.count << e;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, d, A, max_rank, piece,
+                       piece >= kPieceLog2 ? 1 : 0, queue, slots);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
 template <int WMAX>
 hlf_status launch_batch_reduce_t(hlf_batch_s *b, const uint8_t *A, int max_rank,
                                  const hlf_batch_params &p, hipStream_t stream) {
+    hipLaunchKernelGGL(hlf::batch_queue_reset_kernel, dim3((b->count + 255) / 256), dim3(256), 0, stream,
+                       b->queue, b->slots, b->count);
+    if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
     return launch_reduce_view<WMAX>(view_of(b), A, max_rank, p, b->queue, b->slots, stream);
 }
 
@@ -1135,7 +1183,7 @@ hlf_status hlf_batch_reduce_noalloc(int32_t count, int32_t max_n, const int32_t 
     d.hash = hash_dev;
     hipLaunchKernelGGL(hlf::noalloc_layout_kernel, dim3(1), dim3(1024), 0, stream, n_dev, count,
                        max_n, n_eff, offs, offs + kNoAllocMaxCount, offs + 2 * kNoAllocMaxCount,
-                       offs + 3 * kNoAllocMaxCount);
+                       offs + 3 * kNoAllocMaxCount, queue, slots);
     if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
     if (max_n <= 64) return launch_reduce_view<1>(d, A_dev, max_rank, p, queue, slots, stream);
     return launch_reduce_view<3>(d, A_dev, max_rank, p, queue, slots, stream);
