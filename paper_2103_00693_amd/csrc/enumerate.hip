@@ -34,43 +34,49 @@ __global__ __launch_bounds__(kVecThreads) void enum_tile_kernel(FactorIn f, VecR
 }
 
 // ---------------------------------------------------------------------------
-// Materialise, W > 1 words per solution: the tile algebra of the one-word
-// kernel with one lane per word.  A tile is 1024 consecutive indices; thread
-// (slot, w) = (tid / WMAX, tid % WMAX) holds word w of the per-lane constants
-// l ^ F(slot + P*u), u < WMAX, P = 1024 / WMAX, and word w of the tile constant
-// F(T << 10); every output word is one XOR and one 8-byte store, and the
-// active lanes of a wave store one contiguous run of words.
+// Materialise, W > 1 words per solution: the output is one run of words, a tile
+// of 2^S consecutive solutions 64 W words or a power of two times that, and a
+// thread writes the same one or two 16-byte pieces of every tile of its
+// workgroup: l ^ F(slot) of their words in registers, F(T << S) stepped from
+// tile to tile.  An odd W lets a piece straddle two solutions.
+//
+// Bound by HBM writes, and like the one-word kernels (stage2.h) by their order
+// and by a wave's set-up, here some 20 reads of LDS per piece, beside it.
+// 268 MB of 2 words 40.6 us (6.6 TB/s), 403 MB of 3 words 73.6, 101 MB of 11
+// words 21, 1 GiB of 16 words 178 (6.0 TB/s); with one 8-byte nontemporal
+// store per word, the lanes of a power of two of words per solution and 256 KiB
+// per workgroup: 59, 138, 36, 182.
 // ---------------------------------------------------------------------------
-template <int WMAX>
-__global__ __launch_bounds__(kTileThreads) void enum_wide_tile_kernel(FactorIn f, uint64_t begin,
-                                                                      uint64_t count,
-                                                                      uint64_t *__restrict__ out,
-                                                                      uint64_t tiles_per_block,
-                                                                      int counter) {
-    constexpr int P = kTileThreads / WMAX;  // solutions per row of the tile
-    constexpr int U = WMAX;                 // rows per tile
-    constexpr int S = kLogTileThreads;      // log2(P * U)
-    constexpr int LOGP = S - (WMAX == 2 ? 1 : WMAX == 4 ? 2 : WMAX == 8 ? 3 : 4);
-    __shared__ uint64_t Bx[64 * WMAX];
+template <int W>
+struct WideTile {
+    static constexpr int S = W <= 4 ? 8 : W <= 8 ? 7 : 6;  // log2 solutions per tile
+    static constexpr int kPieces = (W << S) / 2;           // at most 512
+    static constexpr int kPer = (kPieces + kVecThreads - 1) / kVecThreads;
+    static constexpr uint64_t kBytes = 8ull * W << S;
+};
+
+template <int W>
+__global__ __launch_bounds__(kVecThreads) void enum_wide_tile_kernel(FactorIn f, uint64_t begin, uint64_t count,
+                                                                     uint64_t *__restrict__ out,
+                                                                     uint64_t tiles_per_block, int counter) {
+    using Tile = WideTile<W>;
+    constexpr int S = Tile::S;
+    __shared__ __align__(16) uint64_t Bx[64 * W];
     int r;
     if (!gate(f, begin, count, r)) return;
-    const int W = f.words;
-    for (int idx = threadIdx.x; idx < 64 * WMAX; idx += blockDim.x) {
-        const int j = idx / WMAX, w = idx - j * WMAX;
-        Bx[idx] = (j < r && w < W) ? f.basis[(size_t)j * W + w] : 0ull;
-    }
+    load_basis_padded<W>(f.basis, r, Bx, threadIdx.x, kVecThreads);
     __syncthreads();
     if (counter) {
-        // Prefix sums B_0 ^ ... ^ B_j (j < r) of word w, by wave w.
-        const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        if (wv < W) {
-            uint64_t v = Bx[lane * WMAX + wv];
+        // Prefix sums B_0 ^ ... ^ B_j (j < r), a word per wave.
+        const int lane = threadIdx.x & 63;
+        for (int w = threadIdx.x >> 6; w < W; w += kVecThreads / 64) {
+            uint64_t v = Bx[lane * W + w];
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
                 const uint64_t t = __shfl_up(v, d);
                 if (lane >= d) v ^= t;
             }
-            if (lane < r) Bx[lane * WMAX + wv] = v;
+            if (lane < r) Bx[lane * W + w] = v;
         }
         __syncthreads();
     }
@@ -79,35 +85,69 @@ __global__ __launch_bounds__(kTileThreads) void enum_wide_tile_kernel(FactorIn f
     const uint64_t t0 = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * tiles_per_block;
     if (t0 >= ntiles) return;
     const uint64_t t1 = (t0 + tiles_per_block < ntiles) ? t0 + tiles_per_block : ntiles;
-
-    const int w = (int)(threadIdx.x & (WMAX - 1));
-    const int slot = (int)(threadIdx.x / WMAX);
-    // lo[u] = l ^ F(slot + P*u): F(P * 2^k) = E_{LOGP + k}, built along u.
-    uint64_t lo[U];
-    lo[0] = ((w < W) ? f.shift[w] : 0ull) ^ F_low<WMAX>(Bx, (uint64_t)slot, LOGP, w);
-#pragma unroll
-    for (int u = 1; u < U; ++u)
-        lo[u] = lo[u & (u - 1)] ^ E_at<WMAX>(Bx, LOGP + __builtin_ctz(u), w);
     uint64_t Tt = (begin >> S) + t0;
-    uint64_t hi = F_tile<WMAX>(Bx, Tt, S, w);
-    const bool act = w < W;
+    // l ^ F(i) of a piece's words is l ^ the B_j over the bits j of i ^ (i >> 1).
+    int slot[Tile::kPer][2], w[Tile::kPer][2];
+    uint64_t z[Tile::kPer][2];  // the words of tile Tt
+    auto add = [&](int j, uint64_t mask0, uint64_t mask1, int k) {
+        if constexpr (W % 2 == 0) {  // two words of one solution, side by side
+            const ulonglong2 b = *reinterpret_cast<const ulonglong2 *>(&Bx[j * W + w[k][0]]);
+            z[k][0] ^= b.x & mask0;
+            z[k][1] ^= b.y & mask1;
+        } else {
+            z[k][0] ^= Bx[j * W + w[k][0]] & mask0;
+            z[k][1] ^= Bx[j * W + w[k][1]] & mask1;
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < Tile::kPer; ++k) {
+        uint64_t gray[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = 2 * ((int)threadIdx.x + k * kVecThreads) + h;
+            slot[k][h] = e / W;
+            w[k][h] = e - slot[k][h] * W;
+            z[k][h] = f.shift[w[k][h]];
+            gray[h] = (uint64_t)(slot[k][h] ^ (slot[k][h] >> 1));
+        }
+#pragma unroll
+        for (int j = 0; j < S; ++j) add(j, 0ull - ((gray[0] >> j) & 1), 0ull - ((gray[1] >> j) & 1), k);
+    }
+    for (uint64_t g = (Tt << S) ^ (Tt << S >> 1); g; g &= g - 1) {  // Tt < 2^(62 - S)
+        const int j = __builtin_ctzll(g);
+#pragma unroll
+        for (int k = 0; k < Tile::kPer; ++k) add(j, ~0ull, ~0ull, k);
+    }
     for (uint64_t t = t0; t < t1; ++t, ++Tt) {
         const uint64_t base = Tt << S;
+        uint64_t *o = out + ((int64_t)base - (int64_t)begin) * W;
         if (base >= begin && base + (1u << S) <= end) {
-            if (act) {
-                uint64_t *o = out + (base - begin + (uint64_t)slot) * W + w;
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    __builtin_nontemporal_store(lo[u] ^ hi, o + (uint64_t)u * P * W);
+            for (int k = 0; k < Tile::kPer; ++k) {
+                const int piece = (int)threadIdx.x + k * kVecThreads;
+                if (Tile::kPieces % kVecThreads != 0 && piece >= Tile::kPieces) break;
+                const u32x4 v = {(uint32_t)z[k][0], (uint32_t)(z[k][0] >> 32), (uint32_t)z[k][1],
+                                 (uint32_t)(z[k][1] >> 32)};
+                *reinterpret_cast<u32x4_any *>(o + 2 * piece) = v;
             }
-        } else if (act) {
+        } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint64_t i = base + (uint64_t)slot + (uint64_t)u * P;
-                if (i >= begin && i < end) out[(i - begin) * W + w] = lo[u] ^ hi;
+            for (int k = 0; k < Tile::kPer; ++k) {
+                const int piece = (int)threadIdx.x + k * kVecThreads;
+                if (piece >= Tile::kPieces) break;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint64_t i = base + (uint64_t)slot[k][h];
+                    if (i >= begin && i < end) o[2 * piece + h] = z[k][h];
+                }
             }
         }
-        hi ^= tile_step<WMAX>(Bx, Tt, S, w);
+        const int c = min(S + __builtin_ctzll(Tt + 1), 63);  // the step to the next tile
+#pragma unroll
+        for (int k = 0; k < Tile::kPer; ++k) {
+            add(S - 1, ~0ull, ~0ull, k);
+            add(c, ~0ull, ~0ull, k);
+        }
     }
 }
 
@@ -369,6 +409,11 @@ uint64_t tiles_per_unit_for(uint64_t ntiles, uint64_t max_units, uint64_t *units
 }
 
 // Materialise launches: materialise_tiles_per_block tiles per workgroup.
+// The multi-word circuit kernel's workgroups build per-word tables before their
+// first store, so they take ranges kWideRangeFactor times longer than the
+// common size (passed as a smaller nominal tile size).
+constexpr uint64_t kWideRangeFactor = 2;
+
 uint64_t tiles_per_block_for(uint64_t ntiles, uint64_t tile_bytes, uint64_t *blocks) {
     const uint64_t tpb = materialise_tiles_per_block(ntiles, tile_bytes);
     *blocks = ntiles ? (ntiles + tpb - 1) / tpb : 1;
@@ -388,22 +433,31 @@ hlf_status launch_tile(const FactorIn &f, uint64_t begin, uint64_t count, T *out
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
-// The multi-word kernel's workgroups build per-word tables before their first
-// store, so they take ranges kWideRangeFactor times longer than the W = 1
-// kernels (passed as a smaller nominal tile size).
-constexpr uint64_t kWideRangeFactor = 2;
+// Bytes per workgroup of the multi-word materialise kernel (1 GiB of 16 words:
+// 178 us at 32 KiB, 182 at 64, 187 at 128; 252 MB of 15 words: 44.7, 41.6, 41.0).
+constexpr uint64_t kWideBytes = 32ull << 10;
 
-template <int WMAX>
-hlf_status launch_wide_tile(const FactorIn &f, uint64_t begin, uint64_t count, uint64_t *out,
-                            int counter, hipStream_t stream) {
-    constexpr int S = kLogTileThreads;
+template <int W>
+hlf_status launch_wide_tile(const FactorIn &f, uint64_t begin, uint64_t count, uint64_t *out, int counter,
+                            hipStream_t stream) {
+    constexpr int S = WideTile<W>::S;
     const uint64_t end = begin + count;
     const uint64_t ntiles = (end < begin) ? 1 : ((end - 1) >> S) - (begin >> S) + 1;
-    uint64_t blocks;
-    const uint64_t tpb = tiles_per_block_for(ntiles, (8ull * (uint64_t)f.words << S) / kWideRangeFactor, &blocks);
-    hipLaunchKernelGGL(enum_wide_tile_kernel<WMAX>, dim3((unsigned)blocks), dim3(kTileThreads), 0,
-                       stream, f, begin, count, out, tpb, counter);
+    const uint64_t spread = 8ull * (uint64_t)device_cu_count();
+    uint64_t tpb = std::min(kWideBytes / WideTile<W>::kBytes, (ntiles + spread - 1) / spread);
+    tpb = std::max(tpb, (ntiles + kMaxVecBlocks - 1) / kMaxVecBlocks);
+    const uint64_t blocks = (ntiles + tpb - 1) / tpb;
+    hipLaunchKernelGGL(enum_wide_tile_kernel<W>, dim3((unsigned)blocks), dim3(kVecThreads), 0, stream, f, begin,
+                       count, out, tpb, counter);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
+}
+
+template <int... Ws>
+hlf_status launch_wide(int W, const FactorIn &f, uint64_t begin, uint64_t count, uint64_t *out, int counter,
+                       hipStream_t stream, std::integer_sequence<int, Ws...>) {
+    hlf_status st = HLF_EINVAL;
+    ((W == Ws + 2 ? (st = launch_wide_tile<Ws + 2>(f, begin, count, out, counter, stream), 0) : 0), ...);
+    return st;
 }
 
 template <int WMAX>
@@ -460,10 +514,7 @@ hlf_status launch_enumerate(const FactorIn &f, uint64_t begin, uint64_t count, i
     }
     uint64_t *o = (uint64_t *)out;
     if (((uintptr_t)out & 7u) == 0) {
-        if (W <= 2) return launch_wide_tile<2>(f, begin, count, o, c, stream);
-        if (W <= 4) return launch_wide_tile<4>(f, begin, count, o, c, stream);
-        if (W <= 8) return launch_wide_tile<8>(f, begin, count, o, c, stream);
-        return launch_wide_tile<16>(f, begin, count, o, c, stream);
+        return launch_wide(W, f, begin, count, o, c, stream, std::make_integer_sequence<int, HLF_MAX_N / 64 - 1>{});
     }
     if (W <= 2) return launch_general<2>(f, begin, count, o, c, stream);
     if (W <= 4) return launch_general<4>(f, begin, count, o, c, stream);
