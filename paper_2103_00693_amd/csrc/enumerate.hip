@@ -524,37 +524,34 @@ hlf_status launch_enumerate(const FactorIn &f, uint64_t begin, uint64_t count, i
 
 // ---------------------------------------------------------------------------
 // The paper's circuit for grids of more than 64 vertices (W > 1 words per
-// vector; the same layers as circuit_tile_kernel).  First one workgroup checks
+// vector; the same layers as circuit_tile_kernel).  First a launch checks
 // that A is a subgraph of the N x N grid (every row's bits lie on the vertex
 // itself and its grid neighbours) and writes HLF_EINVAL otherwise, so the
-// materialising launch behind it on the stream writes nothing.  The
-// materialising kernel takes one lane per word, as enum_wide_tile_kernel:
-// thread (slot, w) holds word w of solutions base + slot + u*P, u < WMAX,
+// materialising launch behind it on the stream writes nothing (one thread per
+// word of A; one workgroup for all took 9.7 us at n = 1024).  The materialising
+// kernel takes one lane per word: thread (slot, w) holds word w of solutions base + slot + u*P, u < WMAX,
 // P = 1024 / WMAX.  R, the counter bits scattered onto the pivots, is linear
 // in the index: R = Rlo(slot + u*P) ^ Rhi(T) for a tile T of 1024 indices.
 // The edge layers shift R by 1 and by N bits across words; a lane takes the
 // neighbouring words of its solution from lanes w - 1 and w + 1.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void circuit_check_kernel(int32_t *status, const uint64_t *__restrict__ rows,
-                                                             int n, int W, int N) {
+__global__ __launch_bounds__(256) void circuit_check_kernel(int32_t *status, const uint64_t *__restrict__ rows,
+                                                            int n, int W, int N) {
     if (*(volatile int32_t *)status != HLF_OK) return;
-    int bad = 0;
-    for (int v = threadIdx.x; v < n; v += blockDim.x) {
-        const int gr = v / N, gc = v - (v / N) * N;
-        for (int w = 0; w < W; ++w) {
-            uint64_t allowed = 0;
-            auto allow = [&](int u) {
-                if ((u >> 6) == w) allowed |= 1ull << (u & 63);
-            };
-            allow(v);
-            if (gc > 0) allow(v - 1);
-            if (gc < N - 1) allow(v + 1);
-            if (gr > 0) allow(v - N);
-            if (gr < N - 1) allow(v + N);
-            if (rows[(size_t)v * W + w] & ~allowed) bad = 1;
-        }
-    }
-    if (__syncthreads_or(bad) && threadIdx.x == 0) *status = HLF_EINVAL;
+    const int idx = blockIdx.x * 256 + threadIdx.x;  // one word of A each
+    if (idx >= n * W) return;
+    const int v = idx / W, w = idx - v * W;
+    const int gr = v / N, gc = v - gr * N;
+    uint64_t allowed = 0;
+    auto allow = [&](int u) {
+        if ((u >> 6) == w) allowed |= 1ull << (u & 63);
+    };
+    allow(v);
+    if (gc > 0) allow(v - 1);
+    if (gc < N - 1) allow(v + 1);
+    if (gr > 0) allow(v - N);
+    if (gr < N - 1) allow(v + N);
+    if (rows[idx] & ~allowed) *status = HLF_EINVAL;
 }
 
 namespace {
@@ -696,7 +693,8 @@ hlf_status launch_circuit(const FactorIn &f, const int32_t *pivots, const uint64
     if (word_bits == 64 && f.words == 1) return go(uint64_t{});
     // W > 1 words per solution
     const int W = f.words;
-    hipLaunchKernelGGL(circuit_check_kernel, dim3(1), dim3(1024), 0, stream, f.status, rows, f.n, W, N);
+    hipLaunchKernelGGL(circuit_check_kernel, dim3((unsigned)((f.n * W + 255) / 256)), dim3(256), 0, stream, f.status,
+                       rows, f.n, W, N);
     if (hipGetLastError() != hipSuccess) return HLF_EDEVICE;
     auto wide = [&](auto wm) -> hlf_status {
         constexpr int WMAX = decltype(wm)::value;
