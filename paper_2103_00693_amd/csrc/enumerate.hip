@@ -3,7 +3,8 @@
 //
 //   enum_tile_kernel<T>     W = 1, 16/32/64-bit words, any begin and address:
 //                           one 16-byte store per thread (stage2.h).
-//   enum_wide_tile_kernel   W > 1: the tile algebra with one lane per word.
+//   enum_wide_tile_kernel   W > 1: the same 16-byte pieces of every tile of its
+//                           workgroup per thread.
 //   enum_general_kernel     W > 1 at an address that is not a multiple of 8:
 //                           z_i from LDS lookup tables over the nibbles of i
 //                           (method of four Russians).
@@ -529,8 +530,10 @@ hlf_status launch_enumerate(const FactorIn &f, uint64_t begin, uint64_t count, i
 // itself and its grid neighbours) and writes HLF_EINVAL otherwise, so the
 // materialising launch behind it on the stream writes nothing (one thread per
 // word of A; one workgroup for all took 9.7 us at n = 1024).  The materialising
-// kernel takes one lane per word: thread (slot, w) holds word w of solutions base + slot + u*P, u < WMAX,
-// P = 1024 / WMAX.  R, the counter bits scattered onto the pivots, is linear
+// kernel takes one lane per word: thread (slot, w) holds word w of solutions
+// base + slot + u*P, u < WMAX, P = 1024 / WMAX.  (In pieces of 16 bytes, as
+// enum_wide_tile_kernel, its set-up is too long for the few solutions of a
+// block: 27 MB of 13 words 22 us against 15.)  R, the counter bits scattered onto the pivots, is linear
 // in the index: R = Rlo(slot + u*P) ^ Rhi(T) for a tile T of 1024 indices.
 // The edge layers shift R by 1 and by N bits across words; a lane takes the
 // neighbouring words of its solution from lanes w - 1 and w + 1.

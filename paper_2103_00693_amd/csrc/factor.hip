@@ -303,8 +303,9 @@ __global__ __launch_bounds__(64) void factor_wave_kernel(const uint64_t *__restr
 // of 32 entries of 8 bytes spread over all 64 LDS banks: 530 cycles per word
 // for 1024 rows, against 1080 with tables of 16, which use half of them.
 // Measured at n = 1024 (32x32 grid, half the bonds), stage 1 with the packing:
-// 164 us a pass, against 528 with panels of 8 columns, whose pivots all
-// waves searched together with two barriers a column.
+// 158 us a pass, against 528 with panels of 8 columns, whose pivots all waves
+// searched together with two barriers a column.  (Further candidates filtered
+// by all waves instead of 64 at a time by the one: 173 us.)
 // ---------------------------------------------------------------------------
 constexpr int kTabGroups = 13;                    // groups of five bits of a word
 constexpr int kTabWords = kTabGroups * 32;

@@ -25,17 +25,8 @@ __device__ __forceinline__ uint64_t mix13(uint64_t x) {
     return x;
 }
 
-// mix13 without its first step x ^= x >> 30.  That step is linear over GF(2),
-// so for x = a ^ b it equals (a ^ (a >> 30)) ^ (b ^ (b >> 30)); callers that
-// split x into a per-lane and a per-tile part pre-apply it to each part.
-__device__ __forceinline__ uint64_t mix13_tail(uint64_t x) {
-    x *= 0xBF58476D1CE4E5B9ull;
-    x ^= x >> 27;
-    x *= 0x94D049BB133111EBull;
-    x ^= x >> 31;
-    return x;
-}
-
+// The first step of mix13.  It is linear over GF(2): callers that split x into a
+// per-lane and a per-tile part apply it to each part, and hash_tail does the rest.
 __device__ __forceinline__ uint64_t mix13_head(uint64_t x) { return x ^ (x >> 30); }
 
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane) {
@@ -45,16 +36,6 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane) {
 }
 
 // A value that is the same on every lane, moved to scalar registers.
-// XOR of v over lanes 0..7 of a wave, returned to every lane.  Needs all
-// lanes active.  Three DPP row_shr steps leave the XOR of lanes 0..7 in lane
-// 7 (a disabled source lane contributes the identity 0 through `old`).
-__device__ __forceinline__ uint32_t xor_lanes0to7(uint32_t v) {
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
-    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 7);
-}
-
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
     uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
     uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
@@ -64,12 +45,6 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
-
-__device__ __forceinline__ uint64_t wave_xor_u64(uint64_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v ^= __shfl_xor(v, off, kWave);
     return v;
 }
 
