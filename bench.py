@@ -38,11 +38,11 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # rest of mix13 (2 x [3 multiplies + add3], 2 x [64-bit shift + 2 XOR]), 1 add.
 REDUCE_VALU_OPS_PER_SOLUTION = 17
 # Measured: rocprofv3 --pmc SQ_INSTS_VALU over the four timed reduce launches
-# (ranks 30, 29, 32, 32): 3,032,022,924 wave instructions x 64 lanes /
-# 10,200,547,328 solutions = 19.02 lane operations per solution (the full-tile
+# (ranks 30, 29, 32, 32): 3,132,769,306 wave instructions x 64 lanes /
+# 10,200,547,328 solutions = 19.66 lane operations per solution (the full-tile
 # loop plus per-tile and per-wave work).  The roofline uses it while the
 # kernel's sources are the measured ones, else the loop count above.
-REDUCE_VALU_MEASURED = {"src_sha256_16": "322899540ce79507", "ops_per_solution": 19.02}
+REDUCE_VALU_MEASURED = {"src_sha256_16": "3507b8348f48aa49", "ops_per_solution": 19.66}
 REDUCE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_amd/csrc/enumerate.hip",
                        "paper_2103_00693_amd/csrc/hlf_device.h")
 # Measured: rocprofv3 --pmc SQ_INSTS_VALU (a pass of four counters) over the
@@ -51,15 +51,15 @@ REDUCE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_a
 # workgroup takes the sparse path): 3,302,592 wave instructions x 64 lanes /
 # 65536 samples = 3225.2 lane operations per sample.  Used while the sampler's
 # sources are the measured ones.
-SAMPLE_VALU_MEASURED = {"src_sha256_16": "4c261b6ea9be0de1", "ops_per_sample": 3225.2}
+SAMPLE_VALU_MEASURED = {"src_sha256_16": "0106bbf055f55e35", "ops_per_sample": 3225.2}
 SAMPLE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/sample.hip", "paper_2103_00693_amd/csrc/hlf_device.h")
 # HBM traffic of one batch_enum_kernel<uint32_t, overlap> launch of the headline step,
 # from two rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE, KiB per
 # dispatch), each scaled by what the same counter reads for a plain 256 MiB
 # device copy (WRITE_SIZE 262144 KiB -> x1.0, FETCH_SIZE 131085 KiB -> x2.0).
 # Valid only for the kernel sources it was taken on (sha256 prefix below).
-ENUM_TRAFFIC = {"src_sha256_16": "22ef894c3eb80077", "fetch_kib_raw": 69.2, "fetch_scale": 2.0,
-                "write_kib_raw": 688822.9, "write_scale": 1.0}
+ENUM_TRAFFIC = {"src_sha256_16": "262ccca74928aa31", "fetch_kib_raw": 46.0, "fetch_scale": 2.0,
+                "write_kib_raw": 688130.8, "write_scale": 1.0}
 ENUM_TRAFFIC_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_amd/csrc/batch.hip",
                         "paper_2103_00693_amd/csrc/factor_wave.h",
                         "paper_2103_00693_amd/csrc/hlf_device.h")
@@ -853,10 +853,11 @@ def main():
                 "ranks": ranks,
                 "value": round(rate / 1e9, 2),
                 "unit": "G solutions/s",
-                "roofline": {"bound": "alu", "kernel": "reduce_wave_kernel<1>",
+                "roofline": {"bound": "alu", "kernel": "reduce_kernel<1>",
                              "achieved": round(ops, 2), "peak": round(VALU_PEAK_TOPS, 2),
                              "unit": "T VALU instr-lane-ops/s", "frac": round(ops / VALU_PEAK_TOPS, 4),
-                             "valu_ops_per_solution": per_sol, "valu_ops_source": how},
+                             "valu_ops_per_solution": per_sol, "valu_ops_source": how,
+                             "peak_note": "one instruction per lane and cycle; some 32-bit VOP2 ones issue in pairs"},
             }
 
         def sample_block():
