@@ -58,7 +58,7 @@ SAMPLE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/sample.hip", "paper_2103_00693
 # dispatch), each scaled by what the same counter reads for a plain 256 MiB
 # device copy (WRITE_SIZE 262144 KiB -> x1.0, FETCH_SIZE 131085 KiB -> x2.0).
 # Valid only for the kernel sources it was taken on (sha256 prefix below).
-ENUM_TRAFFIC = {"src_sha256_16": "262ccca74928aa31", "fetch_kib_raw": 46.0, "fetch_scale": 2.0,
+ENUM_TRAFFIC = {"src_sha256_16": "0a147f680c656194", "fetch_kib_raw": 46.8, "fetch_scale": 2.0,
                 "write_kib_raw": 688130.8, "write_scale": 1.0}
 ENUM_TRAFFIC_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_amd/csrc/batch.hip",
                         "paper_2103_00693_amd/csrc/factor_wave.h",

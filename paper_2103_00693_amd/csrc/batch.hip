@@ -631,11 +631,12 @@ constexpr int kPieceLog2 = 17;
 // in turn, without.
 constexpr int kShortPieceLog2 = 12;
 
-int piece_log2(int count, int max_rank, int chunk_log2, int grid) {
+int piece_log2(int count, int max_rank, int chunk_log2, int grid, int *drawn) {
     int most = max_rank;  // log2 of the solutions per wave, at most
     for (int c = count; c > grid; c >>= 1) ++most;
     for (int c = count; c < grid; c <<= 1) --most;
     const int want = std::min(kPieceLog2, std::max(kShortPieceLog2, most - 3));
+    *drawn = want == kPieceLog2;  // also where the caller's chunks are shorter
     int p = chunk_log2;
     while (p > want && claims_fit_count(count, max_rank, p - 1)) --p;
     return p;
@@ -658,12 +659,13 @@ hlf_status launch_reduce_view(const hlf::BatchDev &d, const uint8_t *A, int max_
         per_cu = 1;
     const int waves = std::min(p.waves_per_cu, per_cu);
     int grid = hlf::device_cu_count() * waves;
-    const int piece = piece_log2(d.count, max_rank, p.chunk_log2, grid);
+    int drawn = 0;
+    const int piece = piece_log2(d.count, max_rank, p.chunk_log2, grid, &drawn);
     // no more waves than factor tasks or pieces there can be
     const int e = std::max(max_rank - piece, 0);
     if (e < 20 && (int64_t)d.count << e < grid) grid = d.count << e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, d, A, max_rank, piece,
-                       piece >= kPieceLog2 ? 1 : 0, queue, slots);
+                       drawn, queue, slots);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
