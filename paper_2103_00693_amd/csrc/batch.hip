@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kTileThreads) void batch_solve_kernel(BatchDev b,
         const uint64_t t0 = (uint64_t)(blockIdx.x - t.block0) * t.tiles_per_block;
         if (t0 < ntiles) {
             const uint64_t t1 = (t0 + t.tiles_per_block < ntiles) ? t0 + t.tiles_per_block : ntiles;
-            enum_tiles_w1<T>(Bx, t.shift[0], t.begin, t.count, (T *)t.out, t0, t1);
+            enum_tiles_w1<T, false>(Bx, t.shift[0], t.begin, t.count, (T *)t.out, t0, t1);
         }
     }
     __syncthreads();

@@ -162,9 +162,12 @@ __device__ __forceinline__ void spread16(uint64_t h, uint32_t (&w)[4]) {
 }
 
 // Tiles [t0, t1) (relative to the first tile of [begin, begin+count)) of one
-// instance, by a kTileThreads workgroup; out[i - begin] = z_i.  Requires
+// instance, by a kTileThreads workgroup; out[i - begin] = z_i.  Stores are
+// nontemporal where workgroups start one behind the other (a solve of eight
+// instances: 137 us, 155 with plain ones) and plain where one generation of
+// them writes it all (solve.hip).  Requires
 // begin % V == 0 and a 16-byte aligned `out`.  Bx: LDS basis (WW = 1).
-template <typename T>
+template <typename T, bool kPlain>
 __device__ void enum_tiles_w1(const uint64_t *Bx, uint64_t l, uint64_t begin, uint64_t count,
                               T *__restrict__ out, uint64_t t0, uint64_t t1) {
     constexpr int V = Vec<T>::V;
@@ -206,7 +209,8 @@ __device__ void enum_tiles_w1(const uint64_t *Bx, uint64_t l, uint64_t begin, ui
             val.y = lw[1] ^ hw[1];
             val.z = lw[2] ^ hw[2];
             val.w = lw[3] ^ hw[3];
-            __builtin_nontemporal_store(val, (u32x4 *)(out + (i0 - begin)));
+            if constexpr (kPlain) *(u32x4 *)(out + (i0 - begin)) = val;
+            else __builtin_nontemporal_store(val, (u32x4 *)(out + (i0 - begin)));
         } else {
 #pragma unroll
             for (int e = 0; e < V; ++e) {
