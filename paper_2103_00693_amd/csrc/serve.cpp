@@ -473,7 +473,8 @@ void worker_main(hlf_server_s *s) {
             }
             if (a->phase == 1) {
                 a->rec.status = s->heads[2 * k];
-                a->rec.rank = s->heads[2 * k + 1];
+                // a rejected matrix leaves the record's rank unwritten
+                a->rec.rank = a->rec.status == HLF_OK ? s->heads[2 * k + 1] : 0;
                 // the dense input and packed rows are no longer needed
                 s->dev.release(a->a_off);
                 s->dev.release(a->rows_off);
