@@ -219,7 +219,9 @@ hlf_status hlf_enumerate_circuit(const hlf_factors *f, const uint64_t *rows_dev,
  *   hash_dev    dev uint64 [1]: sum of h(z_i) mod 2^64;
  *   xorfold_dev dev uint64 [W] or NULL: XOR of all z_i.
  * Outputs are overwritten, or added to (counts, hash: mod 2^64; xorfold: XOR)
- * with HLF_ACCUMULATE, so disjoint ranges can be reduced one after another.
+ * with HLF_ACCUMULATE, so disjoint ranges can be reduced one after another, or
+ * beside each other on several streams (the additions are atomic; only the
+ * call that overwrites must come first).
  * Device errors as hlf_enumerate.  count = 0 with overwrite zeroes the outputs. */
 hlf_status hlf_enumerate_reduce(const hlf_factors *f, uint64_t begin, uint64_t count,
                                 uint32_t flags, uint64_t *counts_dev, uint64_t *hash_dev,

@@ -352,8 +352,13 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_kernel(FactorIn f, uint
         uint32_t odd;
         const uint64_t c = range_count(col, (uint32_t)(f.shift[w] >> lane) & 1u, begin, end, odd);
         const uint64_t fold = __ballot(odd);
-        if (j < f.n) counts[j] = accumulate ? counts[j] + c : c;
-        if (xorfold && lane == 0) xorfold[w] = accumulate ? xorfold[w] ^ fold : fold;
+        if (accumulate) {  // launches on other streams may add to the same outputs
+            if (j < f.n && c) atomicAdd((unsigned long long *)&counts[j], (unsigned long long)c);
+            if (xorfold && lane == 0 && fold) atomicXor((unsigned long long *)&xorfold[w], (unsigned long long)fold);
+        } else {
+            if (j < f.n) counts[j] = c;
+            if (xorfold && lane == 0) xorfold[w] = fold;
+        }
         return;
     }
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
