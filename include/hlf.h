@@ -301,8 +301,10 @@ typedef struct hlf_batch_layout {
 } hlf_batch_layout;
 
 /* Launch parameters of hlf_batch_reduce: chunks of 2^chunk_log2 solutions
- * (10..30) are the largest unit of dynamic scheduling; waves_per_cu (1..16) sizes the
- * persistent grid.  hlf_batch_tune picks both by timing the real batch.       */
+ * (10..30) are the largest unit of scheduling (the call takes shorter pieces of
+ * its own, 2^17 or down to 2^12 solutions for small batches); waves_per_cu
+ * (1..16) sizes the persistent grid.  hlf_batch_tune picks both by timing the
+ * real batch.                                                                 */
 typedef struct hlf_batch_params {
     int32_t chunk_log2;
     int32_t waves_per_cu;
@@ -377,9 +379,10 @@ hlf_status hlf_batch_reduce(hlf_batch b, const uint8_t *A_dev, int32_t max_rank,
 /* Autotuner: times hlf_batch_reduce on this batch over a grid of
  * (chunk_log2, waves_per_cu) candidates on `stream` (synchronising it) and
  * stores the fastest as the batch default; *best and *best_ms receive it.
- * Every candidate produces the same results.  Candidates whose chunk count
- * would not fit the queue (see hlf_batch_reduce) are skipped; HLF_EINVAL if
- * none fits.                                                                  */
+ * Every candidate produces the same results.  Candidates that come to the same
+ * launch are timed once, under the largest of their chunk sizes; candidates
+ * whose chunk count would not fit the queue (see hlf_batch_reduce) are
+ * skipped; HLF_EINVAL if none fits.                                           */
 hlf_status hlf_batch_tune(hlf_batch b, const uint8_t *A_dev, int32_t max_rank,
                           hlf_batch_params *best, float *best_ms, hipStream_t stream);
 

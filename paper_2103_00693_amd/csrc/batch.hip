@@ -646,26 +646,36 @@ bool claims_fit(const hlf_batch_s *b, int max_rank, int chunk_log2) {
     return claims_fit_count(b->count, max_rank, chunk_log2);
 }
 
+// What a reduce launches for given parameters.
+struct ReducePlan {
+    int piece, drawn, grid;
+    bool operator==(const ReducePlan &o) const { return piece == o.piece && drawn == o.drawn && grid == o.grid; }
+};
+
+template <int WMAX>
+ReducePlan reduce_plan(int count, int max_rank, const hlf_batch_params &p) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hlf::batch_reduce_kernel<WMAX>, 64, 0) != hipSuccess ||
+        per_cu < 1)
+        per_cu = 1;
+    ReducePlan plan;
+    plan.grid = hlf::device_cu_count() * std::min(p.waves_per_cu, per_cu);
+    plan.piece = piece_log2(count, max_rank, p.chunk_log2, plan.grid, &plan.drawn);
+    // no more waves than factor tasks or pieces there can be
+    const int e = std::max(max_rank - plan.piece, 0);
+    if (e < 20 && (int64_t)count << e < plan.grid) plan.grid = count << e;
+    return plan;
+}
+
 // The persistent factor/reduce kernel over the instances of a device view,
 // with the given queue and slot arrays, which have been reset.
 template <int WMAX>
 hlf_status launch_reduce_view(const hlf::BatchDev &d, const uint8_t *A, int max_rank,
                               const hlf_batch_params &p, hlf::QueueHead *queue,
                               hlf::ChunkSlot *slots, hipStream_t stream) {
-    auto kern = hlf::batch_reduce_kernel<WMAX>;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, 0) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    const int waves = std::min(p.waves_per_cu, per_cu);
-    int grid = hlf::device_cu_count() * waves;
-    int drawn = 0;
-    const int piece = piece_log2(d.count, max_rank, p.chunk_log2, grid, &drawn);
-    // no more waves than factor tasks or pieces there can be
-    const int e = std::max(max_rank - piece, 0);
-    if (e < 20 && (int64_t)d.count << e < grid) grid = d.count << e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, d, A, max_rank, piece,
-                       drawn, queue, slots);
+    const ReducePlan plan = reduce_plan<WMAX>(d.count, max_rank, p);
+    hipLaunchKernelGGL(hlf::batch_reduce_kernel<WMAX>, dim3(plan.grid), dim3(64), 0, stream, d, A, max_rank,
+                       plan.piece, plan.drawn, queue, slots);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
@@ -1022,8 +1032,11 @@ hlf_status hlf_batch_tune(hlf_batch b, const uint8_t *A_dev, int32_t max_rank,
         (void)hipEventDestroy(e0);
         return HLF_EDEVICE;
     }
-    const int chunks[] = {14, 16, 18, 20, 22};
+    // Several chunk sizes come to one launch (piece_log2): the largest of them
+    // stands for it, which leaves the most room for a later call's max_rank.
+    const int chunks[] = {22, 20, 18, 16, 14};
     const int waves[] = {2, 4, 8, 12};
+    std::vector<ReducePlan> timed;
     hlf_batch_params bestp = b->tuned;
     float bestt = 1e30f;
     hlf_status st = HLF_OK;
@@ -1033,6 +1046,9 @@ hlf_status hlf_batch_tune(hlf_batch b, const uint8_t *A_dev, int32_t max_rank,
         any = true;
         for (int w : waves) {
             const hlf_batch_params p = {c, w};
+            const ReducePlan plan = b->max_n <= 64 ? reduce_plan<1>(b->count, max_rank, p) : reduce_plan<3>(b->count, max_rank, p);
+            if (std::find(timed.begin(), timed.end(), plan) != timed.end()) continue;
+            timed.push_back(plan);
             st = batch_reduce_impl(b, A_dev, max_rank, p, stream);  // warm
             if (st != HLF_OK) break;
             float tsum = 0;
