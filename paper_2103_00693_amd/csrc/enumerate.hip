@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void enum_general_kernel(FactorIn f, uint64_t 
             const int d = (int)((i >> (m * G::kDigitBits)) & (G::kEntries - 1));
             z ^= g.tab[(m * G::kEntries + d) * WMAX + w];
         }
-        if (w < W) out[j * W + w] = z;
+        if (w < W) *reinterpret_cast<AnyAddress<uint64_t>::type *>(out + (j * W + w)) = z;
     }
 }
 

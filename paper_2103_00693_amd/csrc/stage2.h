@@ -251,7 +251,12 @@ constexpr int kLogVecThreads = 8;
 // A launch has at most 2^31 threads; longer ranges take more tiles each.
 constexpr uint64_t kMaxVecBlocks = 1ull << 23;
 
-typedef u32x4 u32x4_any __attribute__((aligned(1)));  // a 16-byte store at any address
+// Stores at any address: the output of a call may lie at any byte.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+template <typename T>
+struct AnyAddress {
+    typedef T type __attribute__((aligned(1)));
+};
 
 template <typename T>
 struct VecTile {
@@ -342,7 +347,7 @@ __device__ __forceinline__ void vec_put(const VecRange &g, uint32_t t, uint64_t 
         const u32x4 val = {w[0], w[1], w[2], w[3]};
         *reinterpret_cast<u32x4_any *>(base + off) = val;
     } else {
-        T *o = reinterpret_cast<T *>(base + off);
+        typename AnyAddress<T>::type *o = reinterpret_cast<typename AnyAddress<T>::type *>(base + off);
 #pragma unroll
         for (int e = 0; e < VecTile<T>::V; ++e) {
             if (i0 + e >= g.begin && i0 + e < g.end) {
