@@ -27,7 +27,7 @@ ARCH = os.environ.get("HLF_OFFLOAD_ARCH", "gfx950")
 COMMON = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-function",
+    "-Wall",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
 

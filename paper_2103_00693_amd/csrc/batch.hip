@@ -591,17 +591,6 @@ hlf::BatchDev view_of(const hlf_batch_s *b) {
     return d;
 }
 
-hlf::FactorIn instance_view(const hlf_batch_s *b, int i) {
-    hlf::FactorIn f;
-    f.n = b->n[i];
-    f.words = (b->n[i] + 63) / 64;
-    f.status = b->status + i;
-    f.rank = b->rank + i;
-    f.basis = b->basis + b->mat_off[i];
-    f.shift = b->shift + b->vec_off[i];
-    return f;
-}
-
 bool params_ok(const hlf_batch_params &p) {
     return p.chunk_log2 >= 10 && p.chunk_log2 <= 30 && p.waves_per_cu >= 1 && p.waves_per_cu <= 16;
 }

@@ -24,19 +24,17 @@ namespace hlf {
 namespace {
 
 // ---------------------------------------------------------------------------
-// A0: pack + validate for n <= 64 (larger n: the two launches above).  One
-// workgroup of 64*W threads packs A into bit rows in LDS, then checks A = A^T:
-// for column c, the ballot of bit c over the 64 rows held by wave v is word v
-// of column c, which must equal word v of row c.
+// A0: pack + validate for n <= 64 (larger n: the two launches below).  One wave
+// packs A into bit rows in LDS, one word each, and checks A = A^T.
 //
 // Packing: when n is a multiple of 16 and A is 16-byte aligned, each thread
-// loads 16 bytes (columns 16q..16q+15 of one row) per request, kPackU rows in
+// loads 16 bytes (columns 16q..16q+15 of one row) per request, all its rows in
 // flight, and gathers them into 16 bits.  For a 32-bit word x holding four
 // 0/1 bytes b0..b3, (x * 0x10204080) >> 28 = b0 | b1<<1 | b2<<2 | b3<<3: the
 // partial product of b_k with 2^(28-7k) lands on bit 28+k, and every other
 // partial product lands on a distinct bit below 28 or above 31, so there are
 // no carries into bits 28..31.  Any other n falls back to byte loads (lane l
-// loads column 64w+l of G rows, one ballot per row).
+// loads column l of G rows, one ballot per row).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t gather4(uint32_t x) { return (x * 0x10204080u) >> 28; }
 
@@ -174,93 +172,59 @@ __global__ __launch_bounds__(64 * kCheckWaves) void pack_check_kernel(const uint
     }
 }
 
-template <int WMAX>
-__global__ __launch_bounds__(64 * WMAX) void pack_dense_kernel(const uint8_t *__restrict__ A, int n,
-                                                               int W, uint64_t *__restrict__ rows,
-                                                               int32_t *__restrict__ status) {
-    __shared__ uint64_t lds[64 * WMAX * WMAX];
-    __shared__ int bad;
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6;
-    const int lane = tid & 63;
-    const int nthr = blockDim.x;
-    const int nwaves = nthr >> 6;
-    int mybad = 0;
-
+__global__ __launch_bounds__(64) void pack_dense_kernel(const uint8_t *__restrict__ A, int n,
+                                                        uint64_t *__restrict__ rows, int32_t *__restrict__ status) {
+    __shared__ uint64_t lds[64];
+    const int lane = threadIdx.x;
+    bool bad = false;
+    lds[lane] = 0;
+    __syncthreads();
     if ((n & 15) == 0 && ((uintptr_t)A & 15u) == 0) {
-        // Pieces of 16 bits; pieces past column n-1 of the last word stay 0.
-        for (int idx = tid; idx < n * W; idx += nthr) lds[idx] = 0;
-        if (tid == 0) bad = 0;
-        __syncthreads();
         uint16_t *l16 = reinterpret_cast<uint16_t *>(lds);
-        const int cpr = n >> 4;             // 16-byte chunks per row, <= 4W
-        const int rpp = nthr / cpr;         // rows per pass, >= 16
-        const int ri = tid / cpr, q = tid - ri * cpr;
+        const int cpr = n >> 4;            // 16-byte chunks per row
+        const int rpp = 64 / cpr;          // rows per pass, >= 16
+        const int ri = lane / cpr, q = lane - ri * cpr;
         const u32x4 *A16 = reinterpret_cast<const u32x4 *>(A);
-        constexpr int kPackU = 16;
+        constexpr int kPasses = 4;         // n <= 64 rows, at least 16 a pass
         if (ri < rpp) {
-            for (int i0 = ri; i0 < n; i0 += kPackU * rpp) {
-                u32x4 v[kPackU];
+            u32x4 v[kPasses];
 #pragma unroll
-                for (int u = 0; u < kPackU; ++u) {
-                    const int i = i0 + u * rpp;
-                    v[u] = (i < n) ? __builtin_nontemporal_load(&A16[(size_t)i * cpr + q])
-                                   : u32x4{0u, 0u, 0u, 0u};
-                }
+            for (int u = 0; u < kPasses; ++u) {
+                const int i = ri + u * rpp;
+                v[u] = i < n ? __builtin_nontemporal_load(&A16[(size_t)i * cpr + q]) : u32x4{0u, 0u, 0u, 0u};
+            }
 #pragma unroll
-                for (int u = 0; u < kPackU; ++u) {
-                    const int i = i0 + u * rpp;
-                    if (i < n) {
-                        mybad |= ((v[u].x | v[u].y | v[u].z | v[u].w) & 0xFEFEFEFEu) != 0u;
-                        const uint32_t m = gather4(v[u].x) | (gather4(v[u].y) << 4) |
-                                           (gather4(v[u].z) << 8) | (gather4(v[u].w) << 12);
-                        l16[i * 4 * W + q] = (uint16_t)m;
-                    }
+            for (int u = 0; u < kPasses; ++u) {
+                const int i = ri + u * rpp;
+                if (i < n) {
+                    bad |= ((v[u].x | v[u].y | v[u].z | v[u].w) & 0xFEFEFEFEu) != 0u;
+                    l16[i * 4 + q] = (uint16_t)(gather4(v[u].x) | (gather4(v[u].y) << 4) |
+                                                (gather4(v[u].z) << 8) | (gather4(v[u].w) << 12));
                 }
             }
         }
     } else {
-        if (tid == 0) bad = 0;
-        __syncthreads();
-        // Wave v packs row groups v, v + nwaves, ... of G rows: lane l loads
-        // byte 64*w + l of the G rows at once (independent loads), then one
-        // ballot per row gives the packed word.
         constexpr int G = 16;
-        for (int i0 = wave * G; i0 < n; i0 += nwaves * G) {
-            for (int w = 0; w < W; ++w) {
-                const int j = 64 * w + lane;
-                uint32_t v[G];
+        for (int i0 = 0; i0 < n; i0 += G) {
+            uint32_t v[G];
 #pragma unroll
-                for (int k = 0; k < G; ++k)
-                    v[k] = (j < n && i0 + k < n) ? (uint32_t)A[(size_t)(i0 + k) * n + j] : 0u;
+            for (int k = 0; k < G; ++k)
+                v[k] = (lane < n && i0 + k < n) ? (uint32_t)A[(size_t)(i0 + k) * n + lane] : 0u;
 #pragma unroll
-                for (int k = 0; k < G; ++k) {
-                    if (i0 + k >= n) break;
-                    mybad |= (v[k] > 1u);
-                    const uint64_t word = __ballot(v[k] == 1u);
-                    if (lane == 0) lds[(i0 + k) * W + w] = word;
-                }
+            for (int k = 0; k < G; ++k) {
+                if (i0 + k >= n) break;
+                bad |= v[k] > 1u;
+                const uint64_t word = __ballot(v[k] == 1u);
+                if (lane == 0) lds[i0 + k] = word;
             }
         }
     }
     __syncthreads();
-
-    // Symmetry: tile pairs (I, J), I <= J < W, spread over the waves.
-    {
-        int pidx = 0;
-        for (int I = 0; I < W; ++I)
-            for (int J = I; J < W; ++J, ++pidx) {
-                if (pidx % nwaves != wave) continue;
-                const int ri = 64 * I + lane, rj = 64 * J + lane;
-                const uint64_t x = (ri < n) ? lds[ri * W + J] : 0ull;
-                const uint64_t y = (rj < n) ? lds[rj * W + I] : 0ull;
-                if (tile_pair_asym(x, y)) mybad = 1;
-            }
-    }
-    if (mybad) bad = 1;
-    __syncthreads();
-    for (int idx = tid; idx < n * W; idx += nthr) rows[idx] = lds[idx];
-    if (tid == 0) *status = bad ? HLF_ENOTSYM : HLF_OK;
+    const uint64_t row = lds[lane];  // zero from row n on
+    if (tile_pair_asym(row, row)) bad = true;
+    if (lane < n) rows[lane] = row;
+    const bool any = __ballot(bad) != 0;
+    if (lane == 0) *status = any ? HLF_ENOTSYM : HLF_OK;
 }
 
 // keep_bad: out.status already holds the pack verdict for these rows; a
@@ -741,14 +705,6 @@ __global__ __launch_bounds__(64 * WMAX) void factor_workgroup_kernel(const uint6
 }
 
 template <int WMAX>
-hlf_status launch_pack_t(const uint8_t *A, int n, int W, uint64_t *rows, int32_t *status,
-                         hipStream_t stream) {
-    hipLaunchKernelGGL(pack_dense_kernel<WMAX>, dim3(1), dim3(64 * W), 0, stream, A, n, W, rows,
-                       status);
-    return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
-}
-
-template <int WMAX>
 hlf_status launch_wave_t(const uint64_t *rows, int n, int W, const FactorOut &out, int keep_bad,
                          hipStream_t stream) {
     hipLaunchKernelGGL(factor_wave_kernel<WMAX>, dim3(1), dim3(64), 0, stream, rows, n, W, out,
@@ -778,7 +734,8 @@ hlf_status launch_pack(const uint8_t *A, int n, int W, uint64_t *rows, int32_t *
                            dim3(64 * kCheckWaves), 0, stream, rows, n, W, status);
         return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
     }
-    return launch_pack_t<1>(A, n, W, rows, status, stream);
+    hipLaunchKernelGGL(pack_dense_kernel, dim3(1), dim3(64), 0, stream, A, n, rows, status);
+    return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
 hlf_status launch_factor(const uint64_t *rows, int n, int W, const FactorOut &out,
