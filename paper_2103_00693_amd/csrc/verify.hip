@@ -135,8 +135,8 @@ __global__ __launch_bounds__(64 * kPairWaves) void pair_stats_mfma_kernel(
 // holds: chunk c of half h is dword string_dword<W>(c, h), nibble t of operand
 // dword d its bit 4t + d.  The kernel vectors are encoded in the same order
 // once per workgroup, up to 256 at a time for n = 1024 (all of them up to
-// n = 512); every further group takes the strings again and leaves those that
-// have failed.  The product is taken with the kernel operand first, so
+// n = 512); every further group takes the strings again, leaves those that have
+// failed, and is not begun by a workgroup that has none left.  The product is taken with the kernel operand first, so
 // accumulator register i of lane l holds the count of kernel vector
 // 8(i/4) + 4(l/32) + i%4 of its 32-chunk for string l % 32.  Two chunks share
 // an accumulator: the first K chunk adds to 2^23 and the second chunk of a
@@ -149,6 +149,8 @@ __global__ __launch_bounds__(64 * kPairWaves) void pair_stats_mfma_kernel(
 // strings (134 MB, 19 us) being hidden.  With one block of 32 strings a wave,
 // words loaded 8 bytes at a time, and a second launch for other n - r: 51 us;
 // n - r = 221: 76 us, and 232 with that second, one-thread-per-string kernel.
+// 2^20 uniform strings, which fail at once, n - r = 724: 30 us, and 69 where
+// all three groups are laid out whether or not a string is left.
 constexpr int kMemMfmaMinWords = 4;
 // Waves per workgroup (one workgroup per CU): what the registers allow.
 template <int W>
@@ -237,12 +239,12 @@ __global__ __launch_bounds__(64 * kMemWavesOf<W>) void membership_mfma_kernel(
             load_string<W>(z + s * W, h, next[k]);
         }
     };
-    int j0 = 0;  // the group's first kernel vector
+    int j0 = 0;          // the group's first kernel vector
+    uint64_t alive = 0;  // lanes that have seen a string pass the group
     do {
         const int left = min(nk - j0, 32 * JC);
         const int jcs = (left + 31) >> 5;  // 32-vector chunks in use
         const bool first = j0 == 0;
-        if (!first) __syncthreads();  // the last group's operand has been read
         if (tid < JC) target[tid] = 0;
         if (tid == 0) taken = kMemWaves;
         __syncthreads();
@@ -282,6 +284,7 @@ __global__ __launch_bounds__(64 * kMemWavesOf<W>) void membership_mfma_kernel(
             if (lane == 0) atomicXor(&target[jc], (uint32_t)odd ^ (uint32_t)(odd >> 32));
         }
         __syncthreads();
+        alive = 0;
         for (uint32_t i = (uint32_t)wave, then; i < blocks; i = then) {
             const uint64_t so = 64 * (blk0 + i) + (uint64_t)lane;  // the string this lane stores
             const bool live = so < num;
@@ -374,9 +377,12 @@ __global__ __launch_bounds__(64 * kMemWavesOf<W>) void membership_mfma_kernel(
             const auto sw = __builtin_amdgcn_permlane32_swap(bad[0], bad[1], false, false);
             const uint32_t verdict = sw[0] | sw[1];
             if (live && (first || verdict)) member[so] = verdict ? 0 : 1;
+            if (j0 + 32 * JC < nk) alive |= __ballot(live && verdict == 0);
         }
         j0 += 32 * JC;
-    } while (j0 < nk);
+        // Another group only for strings that have passed so far.  (The barrier
+        // also says that this group's operand has been read.)
+    } while (j0 < nk && __syncthreads_or(alive != 0));
 }
 
 // n <= 192, one thread per string: member[s] = 1 iff <k_j, z_s> = <k_j, l>
