@@ -43,10 +43,12 @@ __global__ __launch_bounds__(kVecThreads) void enum_tile_kernel(FactorIn f, VecR
 //
 // Bound by HBM writes, and like the one-word kernels (stage2.h) by their order
 // and by a wave's set-up, here some 20 reads of LDS per piece, beside it.
-// 268 MB of 2 words 40.6 us (6.6 TB/s), 403 MB of 3 words 73.6, 101 MB of 11
-// words 21, 1 GiB of 16 words 178 (6.0 TB/s); with one 8-byte nontemporal
+// 268 MB of 2 words 40.6 us (6.6 TB/s), 403 MB of 6 words 70, 369 MB of 11
+// words 65, 1 GiB of 16 words 179 (6.0 TB/s); with one 8-byte nontemporal
 // store per word, the lanes of a power of two of words per solution and 256 KiB
-// per workgroup: 59, 138, 36, 182.
+// per workgroup: 59, 80, 96, 182.  Counter order takes the same set-up: tables
+// of prefix sums for it, six exchanges per word, cost 33 MB of 16 words 15 us
+// (9.5 now).
 // ---------------------------------------------------------------------------
 template <int W>
 struct WideTile {
@@ -56,38 +58,27 @@ struct WideTile {
     static constexpr uint64_t kBytes = 8ull * W << S;
 };
 
-template <int W>
+template <int W, bool kCounter>
 __global__ __launch_bounds__(kVecThreads) void enum_wide_tile_kernel(FactorIn f, uint64_t begin, uint64_t count,
                                                                      uint64_t *__restrict__ out,
-                                                                     uint64_t tiles_per_block, int counter) {
+                                                                     uint64_t tiles_per_block) {
     using Tile = WideTile<W>;
     constexpr int S = Tile::S;
     __shared__ __align__(16) uint64_t Bx[64 * W];
+    // All arguments in one wait, not the last ones behind the barrier.
+    asm volatile("" ::"s"(f.shift), "s"(begin), "s"(count), "s"(out), "s"(tiles_per_block));
     int r;
     if (!gate(f, begin, count, r)) return;
     load_basis_padded<W>(f.basis, r, Bx, threadIdx.x, kVecThreads);
     __syncthreads();
-    if (counter) {
-        // Prefix sums B_0 ^ ... ^ B_j (j < r), a word per wave.
-        const int lane = threadIdx.x & 63;
-        for (int w = threadIdx.x >> 6; w < W; w += kVecThreads / 64) {
-            uint64_t v = Bx[lane * W + w];
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint64_t t = __shfl_up(v, d);
-                if (lane >= d) v ^= t;
-            }
-            if (lane < r) Bx[lane * W + w] = v;
-        }
-        __syncthreads();
-    }
     const uint64_t end = begin + count;
     const uint64_t ntiles = ((end - 1) >> S) - (begin >> S) + 1;
     const uint64_t t0 = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * tiles_per_block;
     if (t0 >= ntiles) return;
     const uint64_t t1 = (t0 + tiles_per_block < ntiles) ? t0 + tiles_per_block : ntiles;
     uint64_t Tt = (begin >> S) + t0;
-    // l ^ F(i) of a piece's words is l ^ the B_j over the bits j of i ^ (i >> 1).
+    // l ^ F(i) of a piece's words is l ^ the B_j over the bits j of i ^ (i >> 1),
+    // or of i itself in counter order.
     int slot[Tile::kPer][2], w[Tile::kPer][2];
     uint64_t z[Tile::kPer][2];  // the words of tile Tt
     auto add = [&](int j, uint64_t mask0, uint64_t mask1, int k) {
@@ -109,12 +100,12 @@ __global__ __launch_bounds__(kVecThreads) void enum_wide_tile_kernel(FactorIn f,
             slot[k][h] = e / W;
             w[k][h] = e - slot[k][h] * W;
             z[k][h] = f.shift[w[k][h]];
-            gray[h] = (uint64_t)(slot[k][h] ^ (slot[k][h] >> 1));
+            gray[h] = (uint64_t)(kCounter ? slot[k][h] : slot[k][h] ^ (slot[k][h] >> 1));
         }
 #pragma unroll
         for (int j = 0; j < S; ++j) add(j, 0ull - ((gray[0] >> j) & 1), 0ull - ((gray[1] >> j) & 1), k);
     }
-    for (uint64_t g = (Tt << S) ^ (Tt << S >> 1); g; g &= g - 1) {  // Tt < 2^(62 - S)
+    for (uint64_t g = (Tt << S) ^ (kCounter ? 0ull : Tt << S >> 1); g; g &= g - 1) {  // Tt < 2^(62 - S)
         const int j = __builtin_ctzll(g);
 #pragma unroll
         for (int k = 0; k < Tile::kPer; ++k) add(j, ~0ull, ~0ull, k);
@@ -143,10 +134,19 @@ __global__ __launch_bounds__(kVecThreads) void enum_wide_tile_kernel(FactorIn f,
                 }
             }
         }
-        const int c = min(S + __builtin_ctzll(Tt + 1), 63);  // the step to the next tile
+        if (t + 1 == t1) break;
+        // The step to the next tile: rows S - 1 and c in Gray order, the rows of
+        // the carry, S to c, in counter order (two of them on average).
+        const int c = min(S + __builtin_ctzll(Tt + 1), 63);
+        if constexpr (kCounter) {
+            for (int j = S; j < c; ++j) {
+#pragma unroll
+                for (int k = 0; k < Tile::kPer; ++k) add(j, ~0ull, ~0ull, k);
+            }
+        }
 #pragma unroll
         for (int k = 0; k < Tile::kPer; ++k) {
-            add(S - 1, ~0ull, ~0ull, k);
+            if constexpr (!kCounter) add(S - 1, ~0ull, ~0ull, k);
             add(c, ~0ull, ~0ull, k);
         }
     }
@@ -439,9 +439,14 @@ hlf_status launch_tile(const FactorIn &f, uint64_t begin, uint64_t count, T *out
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
-// Bytes per workgroup of the multi-word materialise kernel (1 GiB of 16 words:
-// 178 us at 32 KiB, 182 at 64, 187 at 128; 252 MB of 15 words: 44.7, 41.6, 41.0).
+// Tiles per workgroup of the multi-word materialise kernel.  Up to kWideFill
+// tiles each go to one generation of two workgroups per CU: a workgroup's
+// set-up costs several tiles (21 MB of 5 words: 7.1 us in 512 workgroups of 8
+// tiles, 9.5 in 2048 of 2; 8.7 with 128 KiB per 1024-thread workgroup), and a
+// longer range in 32 KiB each, many more workgroups than run at once (1 GiB of
+// 16 words: 178 us at 32 KiB, 182 at 64, 187 at 128; of 15 words within 3%).
 constexpr uint64_t kWideBytes = 32ull << 10;
+constexpr uint64_t kWideFill = 32;
 
 template <int W>
 hlf_status launch_wide_tile(const FactorIn &f, uint64_t begin, uint64_t count, uint64_t *out, int counter,
@@ -449,12 +454,17 @@ hlf_status launch_wide_tile(const FactorIn &f, uint64_t begin, uint64_t count, u
     constexpr int S = WideTile<W>::S;
     const uint64_t end = begin + count;
     const uint64_t ntiles = (end < begin) ? 1 : ((end - 1) >> S) - (begin >> S) + 1;
-    const uint64_t spread = 8ull * (uint64_t)device_cu_count();
-    uint64_t tpb = std::min(kWideBytes / WideTile<W>::kBytes, (ntiles + spread - 1) / spread);
+    const uint64_t resident = 2ull * (uint64_t)device_cu_count();
+    const uint64_t fill = (ntiles + resident - 1) / resident;
+    uint64_t tpb = fill <= kWideFill ? fill : kWideBytes / WideTile<W>::kBytes;
     tpb = std::max(tpb, (ntiles + kMaxVecBlocks - 1) / kMaxVecBlocks);
     const uint64_t blocks = (ntiles + tpb - 1) / tpb;
-    hipLaunchKernelGGL(enum_wide_tile_kernel<W>, dim3((unsigned)blocks), dim3(kVecThreads), 0, stream, f, begin,
-                       count, out, tpb, counter);
+    if (counter)
+        hipLaunchKernelGGL((enum_wide_tile_kernel<W, true>), dim3((unsigned)blocks), dim3(kVecThreads), 0, stream, f,
+                           begin, count, out, tpb);
+    else
+        hipLaunchKernelGGL((enum_wide_tile_kernel<W, false>), dim3((unsigned)blocks), dim3(kVecThreads), 0, stream, f,
+                           begin, count, out, tpb);
     return hipGetLastError() == hipSuccess ? HLF_OK : HLF_EDEVICE;
 }
 
