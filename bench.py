@@ -32,6 +32,11 @@ FP4_MFMA_PEAK_TFLOPS = 10100.0  # dense fp4 (E2M1) matrix-core peak
 # Full-rate 32-bit VALU lane operations per second: 256 CUs x 4 SIMDs x 16
 # lanes x 2.4 GHz.
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+# One-word hashes per second of a loop of them alone (the multiply-add form of
+# the reduce kernel, full occupancy), the most that kernel could reach: some
+# 32-bit VOP2 instructions of two waves issue together, so this is above one
+# instruction per lane and cycle (39.3 / 17 = 2.31 T).
+HASH_LOOP_TOPS = 2.44
 # VALU instructions per solution in the full-tile loop of the reduce kernel
 # (read from its gfx950 assembly): 2 XOR to form the input of the mix13 tail
 # (its GF(2)-linear first step is applied per lane and per tile), 14 for the
@@ -40,8 +45,8 @@ REDUCE_VALU_OPS_PER_SOLUTION = 17
 # Measured: rocprofv3 --pmc SQ_INSTS_VALU over the four timed reduce launches
 # (ranks 30, 29, 32, 32): 3,132,769,306 wave instructions x 64 lanes /
 # 10,200,547,328 solutions = 19.66 lane operations per solution (the full-tile
-# loop plus per-tile and per-wave work).  The roofline uses it while the
-# kernel's sources are the measured ones, else the loop count above.
+# loop plus per-tile and per-wave work).  Reported while the kernel's sources
+# are the measured ones, else the loop count above.
 REDUCE_VALU_MEASURED = {"src_sha256_16": "872bacfaf2878bd3", "ops_per_solution": 19.66}
 REDUCE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_amd/csrc/enumerate.hip",
                        "paper_2103_00693_amd/csrc/hlf_device.h")
@@ -95,9 +100,9 @@ def _sources_sha256_16(paths):
 
 
 def reduce_valu_ops_per_solution():
-    """(VALU lane operations per solution, how it was obtained) for the reduce
-    roofline: the counter measurement while the sources match, else the
-    count of the full-tile loop."""
+    """(VALU lane operations per solution, how it was obtained) of the reduce
+    kernel: the counter measurement while the sources match, else the count
+    of the full-tile loop."""
     if _sources_sha256_16(REDUCE_VALU_SOURCES) == REDUCE_VALU_MEASURED["src_sha256_16"]:
         return REDUCE_VALU_MEASURED["ops_per_solution"], "SQ_INSTS_VALU x 64 / solutions (rocprofv3)"
     return REDUCE_VALU_OPS_PER_SOLUTION, "full-tile loop instruction count (assembly)"
@@ -847,17 +852,16 @@ def main():
             red_sol = sum(1 << r for r in ranks)
             rate = red_sol / red_s
             per_sol, how = reduce_valu_ops_per_solution()
-            ops = rate * per_sol / 1e12
             return {
                 "workload": "N=6 grid (n=36), edges p=0.5, seeds 0-3: counts + hash + xorfold over all 2^r",
                 "ranks": ranks,
                 "value": round(rate / 1e9, 2),
                 "unit": "G solutions/s",
                 "roofline": {"bound": "alu", "kernel": "reduce_kernel<1>",
-                             "achieved": round(ops, 2), "peak": round(VALU_PEAK_TOPS, 2),
-                             "unit": "T VALU instr-lane-ops/s", "frac": round(ops / VALU_PEAK_TOPS, 4),
+                             "achieved": round(rate / 1e12, 3), "peak": HASH_LOOP_TOPS,
+                             "unit": "T solutions/s", "frac": round(rate / 1e12 / HASH_LOOP_TOPS, 4),
                              "valu_ops_per_solution": per_sol, "valu_ops_source": how,
-                             "peak_note": "one instruction per lane and cycle; some 32-bit VOP2 ones issue in pairs"},
+                             "peak_note": "one-word hashes of a loop of them alone, measured"},
             }
 
         def sample_block():

@@ -51,7 +51,8 @@
  *   of it.  The single-instance entry points never allocate; a batch (below)
  *   allocates its own result arrays once, in hlf_batch_create.  Every call is asynchronous on the caller's stream and returns once
  *   the work is enqueued.  Calls on different streams are independent; calls
- *   that write the same buffers must be ordered by the caller.
+ *   that write the same buffers must be ordered by the caller (but for reduces
+ *   that accumulate, see hlf_enumerate_reduce).
  *
  * Errors.  A host-detectable error (NULL pointer, n out of range, bad
  *   word_bits or flags) is returned at once and nothing is enqueued.
@@ -107,7 +108,8 @@ typedef struct hlf_factors {
     int32_t *status;    /* dev [1]: hlf_status of the record                       */
     int32_t *rank;      /* dev [1]: r                                              */
     int32_t *pivots;    /* dev [n]: p_0 < ... < p_{r-1}; entries r..n-1 are -1     */
-    uint64_t *basis;    /* dev [n*W]: rows 0..r-1 hold B_k; other rows untouched   */
+    uint64_t *basis;    /* dev [n*W]: rows 0..r-1 hold B_k; other rows untouched
+                           (their values have no effect, but all n are read)     */
     uint64_t *shift;    /* dev [W]: l                                              */
     uint64_t *kernel;   /* dev [n*W] or NULL: rows 0..n-r-1 hold k_f (f ascending) */
 } hlf_factors;
@@ -139,7 +141,7 @@ hlf_status hlf_pack_dense(const uint8_t *A_dev, int32_t n, uint64_t *rows_dev,
  *              f->kernel may be NULL.  The record is read at call time only.
  * Writes f->status (HLF_OK, HLF_ENOTSYM, or HLF_EINTERNAL), f->rank,
  * f->pivots, f->basis, f->shift and, if not NULL, f->kernel.  Any n up to
- * HLF_MAX_N; n <= 192 runs one wavefront per instance, larger n one workgroup.
+ * HLF_MAX_N; n <= 64 runs one wavefront per instance, larger n one workgroup.
  * Returns HLF_EINVAL for NULL pointers, n out of range or words != ceil(n/64). */
 hlf_status hlf_factor(const uint64_t *rows_dev, const hlf_factors *f, hipStream_t stream);
 
@@ -165,7 +167,8 @@ hlf_status hlf_factor_ex(const uint64_t *rows_dev, const hlf_factors *f, uint32_
  * count > 2^r) in f->status, and nothing is written to out_dev.  count = 0
  * runs stage 1 only.  Every workgroup of the launch factors the instance
  * itself, so no workgroup waits for another: meant for latency-bound small
- * counts (for large counts hlf_factor + hlf_enumerate factor once).
+ * counts (a range of 64 to 256 MiB runs as one generation of workgroups; for
+ * larger ones hlf_factor + hlf_enumerate factor once).
  * Returns HLF_EINVAL for NULL pointers, n > 64, a word size not allowed for n,
  * or a misaligned begin or out_dev.                                            */
 hlf_status hlf_solve_dense(const uint8_t *A_dev, const hlf_factors *f, uint64_t begin,
@@ -175,8 +178,9 @@ hlf_status hlf_solve_dense(const uint8_t *A_dev, const hlf_factors *f, uint64_t 
  * the final CNOT layer): out[i - begin] = z_i for i in [begin, begin + count).
  *   word_bits  16, 32 or 64 when n <= word_bits <= 64: one uint16/uint32/uint64
  *              per solution; or 64*W for any n: W uint64 words per solution.
- *   out_dev    dev buffer of count * word_bits / 8 bytes; the fast path needs
- *              16-byte alignment (any alignment is correct).
+ *   out_dev    dev buffer of count * word_bits / 8 bytes at any address (with
+ *              several words per solution, one that is not a multiple of 8
+ *              takes a slower kernel).
  * Device errors: HLF_ERANGE in f->status if r > 62 or begin + count > 2^r
  * (nothing is written).  count = 0 enqueues nothing and returns HLF_OK.
  * Returns HLF_EINVAL for NULL pointers or word_bits not allowed for n.          */
@@ -187,8 +191,8 @@ hlf_status hlf_enumerate(const hlf_factors *f, uint64_t begin, uint64_t count,
  * z_i = l XOR (XOR over set bits k of i of B_k), the output of the paper's
  * circuit fed by the binary counter of the FPGA design (Section 4); the
  * circuit is defined for the graph of any symmetric A (Section 5), and this
- * is its output for every A (the tile algebra runs on the prefix sums
- * B_0 ^ ... ^ B_k, whose Gray-order walk is the counter order of B).
+ * is its output for every A (the tile algebra selects the rows by the bits of
+ * i instead of i ^ (i >> 1)).
  * Without flags: hlf_enumerate (Gray order).  Arguments, errors as there.
  * Returns HLF_EINVAL for unknown flags.                                         */
 hlf_status hlf_enumerate_ex(const hlf_factors *f, uint64_t begin, uint64_t count,
@@ -322,9 +326,10 @@ hlf_status hlf_batch_destroy(hlf_batch b);
 hlf_status hlf_batch_get_layout(hlf_batch b, hlf_batch_layout *layout);
 
 /* Stage 1 for every instance (pack + validate + factor, Section 1 and
- * Section 2 tasks (1)-(4)): one launch for all instances with n_i <= 192 (a
- * wavefront each), one workgroup launch per larger instance.  A_dev is the
- * concatenated dense input.  Writes every record field of every instance.     */
+ * Section 2 tasks (1)-(4)): one launch per word count for the instances with
+ * n_i <= 192 (a wavefront each), four launches (two to pack, the workgroup
+ * elimination, the verdict) per larger instance.  A_dev is the concatenated
+ * dense input.  Writes every record field of every instance.                  */
 hlf_status hlf_batch_factor_dense(hlf_batch b, const uint8_t *A_dev, hipStream_t stream);
 
 /* Stage 2 materialise for `num` instances at once: out[k][i - begin[k]] = z_i
@@ -481,7 +486,7 @@ hlf_status hlf_server_destroy(hlf_server s);
 /* hlf_batch_reduce without a batch object, for callers that cannot allocate
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * the allocator): the call allocates nothing and frees nothing.  Its scratch
- * (work queue, chunk slots, layout offsets: about 832 KiB) is a device array
+ * (work queue, chunk slots, layout offsets: about 705 KiB) is a device array
  * of the library, one per GPU, kept until the process ends.  Every call on a
  * GPU uses that GPU's array: calls that overlap on one GPU (on different
  * streams) race and must be ordered by the caller.

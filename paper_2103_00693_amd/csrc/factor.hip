@@ -10,7 +10,7 @@
 //   * factor_workgroup_kernel: one workgroup per instance for n <= 1024, one
 //     row per thread in VGPRs, Gauss-Jordan in panels of 64 columns: one wave
 //     finds a panel's pivots on one word per row, then every row applies the
-//     panel with 16 lookups per word in tables of XOR combinations of the
+//     panel with 13 lookups per word in tables of XOR combinations of the
 //     panel's pivot rows (LDS).
 // Both variants produce the canonical record defined in hlf.h (the RREF is
 // unique, so the pivot rows chosen do not matter).

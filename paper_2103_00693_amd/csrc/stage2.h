@@ -81,23 +81,26 @@ struct Vec {
     static constexpr int LOGV = (V == 8) ? 3 : (V == 4) ? 2 : 1;
 };
 
-// Materialise workgroups: 1024 threads, one 16-byte store per thread per
-// tile, so a tile holds 1024*V solutions.
+// Workgroups of the one-launch solve kernels and of the multi-word circuit:
+// 1024 threads; the solve's write one 16-byte store per thread per tile, so a
+// tile holds 1024*V solutions.
 constexpr int kTileThreads = 1024;
 constexpr int kLogTileThreads = 10;
 // Workgroups per CU of the one-launch solve kernel (more workgroups than
 // resident slots: the dispatcher balances the tail).
 constexpr int kTileBlocksPerCU = 16;
-// Materialise kernels give each workgroup a short contiguous range of about
-// kBlockBytes of output, and a launch holds many more workgroups than fit on
-// the device, so the resident ones are at different points of their ranges
-// (resident workgroups that write in step at a fixed stride lose 5-15% of
-// the write bandwidth).  Longer ranges only for grids beyond kMaxTileBlocks.
+// The kernels whose workgroups factor or build tables first (the one-launch
+// solve outside its one-generation sizes, the multi-word circuit) give each
+// workgroup a short contiguous range of about kBlockBytes of output, and a
+// launch holds many more workgroups than fit on the device, so the resident
+// ones are at different points of their ranges (resident workgroups that write
+// in step at a fixed stride lose 5-15% of the write bandwidth).  Longer ranges
+// only for grids beyond kMaxTileBlocks.
 constexpr uint64_t kBlockBytes = 128ull << 10;
 constexpr uint64_t kMaxTileBlocks = 1ull << 30;
 
-// Tiles per workgroup for a materialise launch over ntiles tiles of
-// tile_bytes bytes each; a launch too small to give every CU two workgroups
+// Tiles per workgroup for such a launch over ntiles tiles of tile_bytes bytes
+// each; a launch too small to give every CU two workgroups
 // at that size is spread thinner.
 inline uint64_t materialise_tiles_per_block(uint64_t ntiles, uint64_t tile_bytes) {
     uint64_t want = kBlockBytes / tile_bytes ? kBlockBytes / tile_bytes : 1;
@@ -108,7 +111,7 @@ inline uint64_t materialise_tiles_per_block(uint64_t ntiles, uint64_t tile_bytes
     return need > want ? need : want;
 }
 
-// Bytes of one tile of the W = 1 materialise kernels (one 16-byte store per
+// Bytes of one tile of the one-launch solve kernels (one 16-byte store per
 // thread).
 constexpr uint64_t kTileBytes = 16ull * kTileThreads;
 // Grids up to this many workgroups seed their lane constants the short way.
@@ -119,7 +122,7 @@ constexpr unsigned kShortSeedGrid = 512;
 // each XCD's workgroups take one contiguous run of blocks, in order: XCD x
 // takes the q or q + 1 blocks from x*q + min(x, n % 8) on, q = n / 8.  Stores
 // from one XCD then stay in one region instead of interleaving with the other
-// seven XCDs' every 128 KiB, which the HBM write rate favours.
+// seven XCDs' every workgroup, which the HBM write rate favours.
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n) {
     const uint32_t x = b & 7u, q = n >> 3, rem = n & 7u;
     return x * q + (x < rem ? x : rem) + (b >> 3);
@@ -245,6 +248,14 @@ __device__ void enum_tiles_w1(const uint64_t *Bx, uint64_t l, uint64_t begin, ui
 // 16-byte stores may be misaligned in memory, which costs nothing measurable
 // as long as each XCD writes one contiguous run (xcd_block): dealt in turn,
 // misaligned tiles straddle two XCDs' pages and drop to 4.8 TB/s.
+//
+// These rates hold from idle for about 1.5 ms and again from about 30 ms on;
+// between, the card's power regulation holds back writes of changing data
+// (the same launches writing one value dip to 6.2 TB/s only).  Calls of 8 GiB:
+// 7.4 TB/s at first, 4.9 at 3 to 4 ms, 5.8 at 8 to 12, 7.1 to 7.2 from 32 on;
+// with 128 KiB per workgroup, nontemporal, 5.8 to 6.2 throughout.  The longer
+// form gains 7% over bursts of 3 to 20 ms from idle and loses up to 20% on
+// shorter and longer ones, whatever the size of a call, so no rule takes it.
 // ---------------------------------------------------------------------------
 constexpr int kVecThreads = 256;
 constexpr int kLogVecThreads = 8;
@@ -471,7 +482,7 @@ __device__ __forceinline__ void vec_materialise(int32_t *status, const int32_t *
 
 // ---------------------------------------------------------------------------
 // Reduce.  Per-qubit counts and the XOR-fold of a range follow in closed form
-// (range_counts below), so only the hash visits the solutions: one wavefront
+// (range_count below), so only the hash visits the solutions: one wavefront
 // per contiguous range of indices, tiles of 64 U of them.  A whole tile's
 // solutions are the coset z(T << S) ^ span(B_0 .. B_{S-1}), whichever member
 // of it represents the tile, so from tile T to T + 1 the representative

@@ -162,7 +162,7 @@ class Factors:
         """A record in ONE uninitialised device buffer: status and rank
         adjacent (one 8-byte copy reads both), then pivots, shift, basis and
         the optional kernel vectors.  hlf_factor writes every field that a
-        later call reads (the basis rows past r are not read)."""
+        later call uses (basis rows past r are read, but meet no index bit)."""
         if not 1 <= n <= HLF_MAX_N:
             raise HlfError(HLF_EINVAL, f"n={n} outside [1, {HLF_MAX_N}]")
         self = cls.__new__(cls)
