@@ -254,7 +254,7 @@ __device__ void enum_tiles_w1(const uint64_t *Bx, uint64_t l, uint64_t begin, ui
 // (the same launches writing one value dip to 6.2 TB/s only).  Calls of 8 GiB:
 // 7.4 TB/s at first, 4.9 at 3 to 4 ms, 5.8 at 8 to 12, 7.1 to 7.2 from 32 on;
 // with 128 KiB per workgroup, nontemporal, 5.8 to 6.2 throughout.  The longer
-// form gains 7% over bursts of 3 to 20 ms from idle and loses up to 20% on
+// form gains 7% over bursts of 3 to 20 ms from idle and loses up to 23% on
 // shorter and longer ones, whatever the size of a call, so no rule takes it.
 // ---------------------------------------------------------------------------
 constexpr int kVecThreads = 256;
