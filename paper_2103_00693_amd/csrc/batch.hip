@@ -221,7 +221,8 @@ __global__ __launch_bounds__(kTileThreads) void batch_solve_kernel(BatchDev b,
             const int n = b.n[i];
             const bool badv = wave_load_dense<1>(A + b.dense_off[i], n, 1, sm);
             factor_wave_core<1>(n, 1, badv, record_of(b, i), sm);
-            if (tid == 0) __hip_atomic_store(&flags[i], 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            release_to_device();
+            if (tid == 0) __hip_atomic_store(&flags[i], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     } else if (tid == 0) {
         while (__hip_atomic_load(&flags[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2)
@@ -462,11 +463,12 @@ __global__ __launch_bounds__(64) void batch_reduce_kernel(BatchDev b, const uint
         if (r >= 0 && r <= max_rank) {  // wave-uniform
             // The release makes the record and the zeroed hash visible to
             // whoever reads the entry.
+            release_to_device();
             if (lane == 0) {
                 const unsigned long long nch = r > chunk_log2 ? 1ull << (r - chunk_log2) : 1ull;
                 const unsigned long long old = atomicAdd(&q->claim, (1ull << kClaimShift) | nch);
                 __hip_atomic_store(&slots[old >> kClaimShift].entry,
-                                   (((old & kChunkMask) + 1) << kInstBits) | (unsigned long long)f, __ATOMIC_RELEASE,
+                                   (((old & kChunkMask) + 1) << kInstBits) | (unsigned long long)f, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
         } else if (lane == 0) {

@@ -126,6 +126,17 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// Makes what this wave has written visible to every workgroup of the device
+// before anything that it stores after this (a flag, stored relaxed; its reader
+// takes an acquire fence).  The wait is spelled out: the fence's own wait for
+// the write-back of the L2 is dropped by the compiler where no other access of
+// the wave is outstanding, since it does not count the write-back among them,
+// and a flag stored right behind it was seen before the data.
+__device__ __forceinline__ void release_to_device() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
 // Mask of the valid bits of the last word of an n-bit vector (all ones when

@@ -3,7 +3,8 @@ hardware may keep an order that the source does not ask for, so no run shows a
 missing one).  A wave may leave when no chunk is left for it: it has to decide
 that on one claim word, whose own slots say that no claim is still to come, and
 not on a second counter that nothing orders behind the claims.  A published
-entry has to release the record behind it, and its reader to acquire it.
+entry has to come after a release of the record behind it, and its reader to
+acquire it.
 """
 
 import os
@@ -33,7 +34,8 @@ def test_waves_leave_on_the_claim_word_alone():
 
 def test_entries_release_and_acquire_their_records():
     k = _kernel()
-    stores = re.findall(r"__hip_atomic_store\(&slots\[[^;]*;", k)
-    assert stores and all("__ATOMIC_RELEASE" in s and "SCOPE_AGENT" in s for s in stores), stores
+    assert len(re.findall(r"__hip_atomic_store\(&slots\[", k)) == 1
+    written, stored = k.index("b.hash[f] = 0"), k.index("__hip_atomic_store(&slots[")
+    assert "release_to_device();" in k[written:stored]
     found = k.index("find_slot(slots,")
     assert '__builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent")' in k[found : k.index("b.rank[inst]")]
