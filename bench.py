@@ -47,7 +47,7 @@ REDUCE_VALU_OPS_PER_SOLUTION = 17
 # 10,200,547,328 solutions = 19.66 lane operations per solution (the full-tile
 # loop plus per-tile and per-wave work).  Reported while the kernel's sources
 # are the measured ones, else the loop count above.
-REDUCE_VALU_MEASURED = {"src_sha256_16": "052698a07148c923", "ops_per_solution": 19.66}
+REDUCE_VALU_MEASURED = {"src_sha256_16": "91fbcd87b2ecc2a5", "ops_per_solution": 19.66}
 REDUCE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_amd/csrc/enumerate.hip",
                        "paper_2103_00693_amd/csrc/hlf_device.h")
 # Measured: rocprofv3 --pmc SQ_INSTS_VALU (a pass of four counters) over the
@@ -56,14 +56,14 @@ REDUCE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_a
 # workgroup takes the sparse path): 3,302,592 wave instructions x 64 lanes /
 # 65536 samples = 3225.2 lane operations per sample.  Used while the sampler's
 # sources are the measured ones.
-SAMPLE_VALU_MEASURED = {"src_sha256_16": "0106bbf055f55e35", "ops_per_sample": 3225.2}
+SAMPLE_VALU_MEASURED = {"src_sha256_16": "a9af2c2d9224a0a2", "ops_per_sample": 3225.2}
 SAMPLE_VALU_SOURCES = ("paper_2103_00693_amd/csrc/sample.hip", "paper_2103_00693_amd/csrc/hlf_device.h")
 # HBM traffic of one batch_enum_kernel<uint32_t, overlap> launch of the headline step,
 # from two rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE, KiB per
 # dispatch), each scaled by what the same counter reads for a plain 256 MiB
 # device copy (WRITE_SIZE 262144 KiB -> x1.0, FETCH_SIZE 131085 KiB -> x2.0).
 # Valid only for the kernel sources it was taken on (sha256 prefix below).
-ENUM_TRAFFIC = {"src_sha256_16": "4f5ad8d64704c93d", "fetch_kib_raw": 45.9, "fetch_scale": 2.0,
+ENUM_TRAFFIC = {"src_sha256_16": "c02f38eb37dae922", "fetch_kib_raw": 46.8, "fetch_scale": 2.0,
                 "write_kib_raw": 688130.8, "write_scale": 1.0}
 ENUM_TRAFFIC_SOURCES = ("paper_2103_00693_amd/csrc/stage2.h", "paper_2103_00693_amd/csrc/batch.hip",
                         "paper_2103_00693_amd/csrc/factor_wave.h",

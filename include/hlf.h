@@ -336,7 +336,9 @@ hlf_status hlf_batch_factor_dense(hlf_batch b, const uint8_t *A_dev, hipStream_t
  * of instance inst[k] for i in [begin[k], begin[k] + count[k]).  inst, begin,
  * count and out are host arrays of length num; out[k] are device buffers.
  * word_bits 16/32/64 with n_i <= word_bits for every listed instance.  Device
- * errors go to the instance's status as in hlf_enumerate.                    */
+ * errors go to the instance's status as in hlf_enumerate.  The tasks of a call
+ * run side by side: where an instance is listed more than once, a bad range in
+ * one task may keep the others of that instance from writing.                */
 hlf_status hlf_batch_enumerate(hlf_batch b, int32_t num, const int32_t *inst,
                                const uint64_t *begin, const uint64_t *count, void *const *out,
                                int32_t word_bits, hipStream_t stream);
